@@ -13,7 +13,9 @@
  *     halfway bounce-back on solid walls (Sec. II.C);
  *   - Poisson equation for the potential of ions, wall charges and bead
  *     charges (Eq. poisson), solved by red-black SOR with Chebyshev
- *     acceleration (Sec. II.C) or by red-black multigrid;
+ *     acceleration (Sec. II.C) or, EK_POISSON_MG, directly by Hartley
+ *     transforms in the time loop (sides up to 960) and by red-black
+ *     multigrid in stand-alone solves;
  *   - Langevin beads of a bead-spring chain coupled to the species by
  *     friction through a trilinear interpolation / spreading kernel, advanced
  *     with MD substeps (Sec. II.B, Eq. polymermodel);
@@ -98,7 +100,7 @@ typedef struct {
   double F_ext[3][3];          /* body force per particle [species][xyz]      */
   int32_t poisson_method;      /* EK_POISSON_SOR or EK_POISSON_MG              */
   double poisson_tol;          /* stop when ||b - A psi|| / ||b|| <= tol       */
-  int32_t poisson_max_iter;    /* SOR iterations or multigrid cycles           */
+  int32_t poisson_max_iter;    /* SOR iterations, or cycles of EK_POISSON_MG   */
   int32_t poisson_check_every; /* residual test every k iterations (>= 1)      */
   double rho_jacobi;           /* Jacobi radius for the Chebyshev schedule;
                                   0 selects (2 + cos(2 pi / max(n))) / 3       */

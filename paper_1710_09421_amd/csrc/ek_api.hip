@@ -71,7 +71,7 @@ ek_status check_params(const ek_params* p, std::string& why) {
 
 // Workspace layout (every block 256-byte aligned).
 struct Layout {
-  size_t fA, fB, mask, wall_q, psi, b, partials, ps, stats, keys, vals, beads, mg, mgt, net, guess,
+  size_t fA, fB, mask, wall_q, psi, b, partials, ps, stats, keys, vals, beads, mg, mgt, spec, net, guess,
       psi_old, psi_old2, psi_old3, total;
 };
 
@@ -100,6 +100,7 @@ Layout make_layout(const ek_params* p, int max_beads) {
   L.beads = take(bead_state_bytes(max_beads));
   L.mg = take(mg_workspace_bytes(p->nx, p->ny, p->nz));
   L.mgt = take(p->poisson_method == EK_POISSON_MG ? mg_sweep_bytes(p->nx, p->ny, p->nz) : 0);
+  L.spec = take(p->poisson_method == EK_POISSON_MG ? spectral_bytes(p->nx, p->ny, p->nz) : 0);
   const bool learned = p->warm_start == EK_WS_LEARNED;
   L.net = take(learned ? UNet::bytes(p->nx, p->ny, p->nz, false) : 0);
   L.guess = take(learned ? n * 8 : 0);
@@ -284,6 +285,10 @@ ek_status ek_ctx::poisson(const double* bb, double* x, bool learned, int& iters,
   PoissonScalars h{};
   last_fallback = 0;
   last_consulted = 0;
+  // the time loop solves directly where the sides have a plan; a stand-alone
+  // solve keeps the multigrid cycles, whose number its callers compare starts by
+  const bool direct = p.poisson_method == EK_POISSON_MG && spec.ok && !solo;
+  if (!learned && direct) return spectral_solve(bb, x, h, iters, res, res0, true);
   if (!learned && p.poisson_method == EK_POISSON_MG) {
     // the start's residual stays on the device (the cycles test its flag and
     // skip themselves once converged); the host reads it with the first
@@ -297,6 +302,7 @@ ek_status ek_ctx::poisson(const double* bb, double* x, bool learned, int& iters,
   }
   ek_status st = learned ? learned_start(bb, x, &h) : initial_residual(bb, x, &h);
   if (st) return st;
+  if (direct) return spectral_solve(bb, x, h, iters, res, res0, false);
   if (p.poisson_method == EK_POISSON_MG) return mg_solve(bb, x, h, iters, res, res0);
   return sor_solve(bb, x, h, iters, res, res0);
 }
@@ -551,6 +557,8 @@ ek_status ek_create(const ek_params* p, int32_t max_beads, void* dev_ws, size_t 
     return EK_EHIP;
   }
   c->mg_setup();
+  if (p->poisson_method == EK_POISSON_MG && L.net > L.spec)
+    spectral_setup(c->spec, ws + L.spec, p->nx, p->ny, p->nz, 1.0);
   if (p->warm_start == EK_WS_LEARNED) {
     c->net = new UNet();
     c->net->stream = c->stream;
@@ -581,6 +589,7 @@ void ek_destroy(ek_ctx* ctx) {
   if (ctx->side_join) (void)hipEventDestroy(ctx->side_join);
   for (hipEvent_t e : ctx->events) (void)hipEventDestroy(e);
   ctx->mg_release();
+  if (ctx->spec_graph) (void)hipGraphExecDestroy(ctx->spec_graph);
   delete ctx->net;
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->own_ws) (void)hipFree(ctx->ws);

@@ -6,6 +6,7 @@
 
 #include "ek_internal.h"
 #include "md_table.h"
+#include "spectral.h"
 #include "unet.h"
 
 namespace ek {
@@ -15,6 +16,31 @@ void launch_table_init(int* keys, long long* vals, hipStream_t s);
 void launch_table_init_bits(int* keys, long long* vals, int bits, hipStream_t s);
 size_t mg_workspace_bytes(int nx, int ny, int nz);
 size_t mg_sweep_bytes(int nx, int ny, int nz);
+}  // namespace ek
+
+namespace ek {
+// Records the launches that `enqueue` issues on `stream` into an executable
+// graph; false (and nothing recorded) when that is not possible.
+template <typename F>
+inline bool record_graph(hipStream_t stream, hipGraphExec_t* out, F enqueue) {
+  if (hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  enqueue();
+  hipGraph_t g = nullptr;
+  if (hipStreamEndCapture(stream, &g) != hipSuccess || !g) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const bool ok = hipGraphInstantiate(out, g, nullptr, nullptr, 0) == hipSuccess;
+  (void)hipGraphDestroy(g);
+  if (!ok) {
+    (void)hipGetLastError();
+    *out = nullptr;
+  }
+  return ok;
+}
 }  // namespace ek
 
 // The learned warm start consults the network only when the relative
@@ -141,6 +167,17 @@ struct ek_ctx {
   ek_status mg_vcycle(const double* b, double* x, int* norm_blocks = nullptr, bool start = false,
                       bool first = false);
   bool mg_graphs(const double* b, double* x);
+  // Direct solver of the time loop's periodic problem (spec.ok where the
+  // sides have a plan): one cycle, the solve, and its recorded first cycle.
+  ek::Spectral spec;
+  hipGraphExec_t spec_graph = nullptr;
+  const double* spec_graph_b = nullptr;
+  double* spec_graph_x = nullptr;
+  bool spec_graph_failed = false;
+  void spectral_cycle(const double* b, double* x, bool start);
+  hipGraphExec_t spectral_graph(const double* b, double* x);
+  ek_status spectral_solve(const double* b, double* x, ek::PoissonScalars h, int& iters,
+                           double& res, double& res0, bool start_norms);
   hipGraphExec_t mg_batch_graph(const double* b, double* x, int n, int untested, int opens);
   ek_status poisson(const double* b, double* x, bool learned, int& iters, double& res,
                     double& res0);

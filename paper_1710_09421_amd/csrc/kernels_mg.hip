@@ -1458,29 +1458,6 @@ void ek_ctx::mg_release() {
   mg = nullptr;
 }
 
-// Records the launches that `enqueue` issues on `stream` into an executable
-// graph; false (and nothing recorded) when that is not possible.
-template <typename F>
-static bool record_graph(hipStream_t stream, hipGraphExec_t* out, F enqueue) {
-  if (hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  enqueue();
-  hipGraph_t g = nullptr;
-  if (hipStreamEndCapture(stream, &g) != hipSuccess || !g) {
-    (void)hipGetLastError();
-    return false;
-  }
-  const bool ok = hipGraphInstantiate(out, g, nullptr, nullptr, 0) == hipSuccess;
-  (void)hipGraphDestroy(g);
-  if (!ok) {
-    (void)hipGetLastError();
-    *out = nullptr;
-  }
-  return ok;
-}
-
 // The two cycle graphs for (b, x); false leaves the solve on single launches.
 bool ek_ctx::mg_graphs(const double* bb, double* x) {
   MG& m = *mg;
