@@ -71,7 +71,7 @@ ek_status check_params(const ek_params* p, std::string& why) {
 
 // Workspace layout (every block 256-byte aligned).
 struct Layout {
-  size_t fA, fB, mask, wall_q, psi, b, partials, ps, stats, keys, vals, beads, mg, mgt, spec, net, guess,
+  size_t fA, fB, mask, wall_q, psi, b, partials, ps, stats, keys, vals, beads, mg, mgt, spec, sor, net, guess,
       psi_old, psi_old2, psi_old3, total;
 };
 
@@ -101,6 +101,7 @@ Layout make_layout(const ek_params* p, int max_beads) {
   L.mg = take(mg_workspace_bytes(p->nx, p->ny, p->nz));
   L.mgt = take(p->poisson_method == EK_POISSON_MG ? mg_sweep_bytes(p->nx, p->ny, p->nz) : 0);
   L.spec = take(p->poisson_method == EK_POISSON_MG ? spectral_bytes(p->nx, p->ny, p->nz) : 0);
+  L.sor = take(p->poisson_method == EK_POISSON_SOR ? sor_bytes(p->nx, p->ny, p->nz) : 0);
   const bool learned = p->warm_start == EK_WS_LEARNED;
   L.net = take(learned ? UNet::bytes(p->nx, p->ny, p->nz, false) : 0);
   L.guess = take(learned ? n * 8 : 0);
@@ -201,7 +202,15 @@ ek_status ek_ctx::sor_solve(const double* bb, double* x, PoissonScalars h, int& 
   double omega = 1.0;
   bool first = true;
   const int ce = p.poisson_check_every;
-  int batch = std::max(ce, ((last_iters + ce - 1) / ce) * ce);
+  if (!h.done && sor_team_solve(bb, x, h, it, st)) {
+    if (st) return st;
+  }
+  // the same half sweeps in launches of their own (larger lattices)
+  for (int k = 0; k < 2 * it; ++k) {
+    omega = first ? 1.0 / (1.0 - 0.5 * rj * rj) : 1.0 / (1.0 - 0.25 * rj * rj * omega);
+    first = false;
+  }
+  int batch = std::max(ce, ((last_iters - it + ce - 1) / ce) * ce);
   while (!h.done && it < p.poisson_max_iter) {
     const int nrun = std::min(batch, p.poisson_max_iter - it);
     for (int k = 0; k < nrun; ++k) {
@@ -557,7 +566,8 @@ ek_status ek_create(const ek_params* p, int32_t max_beads, void* dev_ws, size_t 
     return EK_EHIP;
   }
   c->mg_setup();
-  if (p->poisson_method == EK_POISSON_MG && L.net > L.spec)
+  if (p->poisson_method == EK_POISSON_SOR && L.net > L.sor) c->sor_setup(ws + L.sor);
+  if (p->poisson_method == EK_POISSON_MG && L.sor > L.spec)
     spectral_setup(c->spec, ws + L.spec, p->nx, p->ny, p->nz, 1.0);
   if (p->warm_start == EK_WS_LEARNED) {
     c->net = new UNet();

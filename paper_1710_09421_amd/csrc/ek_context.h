@@ -16,6 +16,20 @@ void launch_table_init(int* keys, long long* vals, hipStream_t s);
 void launch_table_init_bits(int* keys, long long* vals, int bits, hipStream_t s);
 size_t mg_workspace_bytes(int nx, int ny, int nz);
 size_t mg_sweep_bytes(int nx, int ny, int nz);
+
+// Tiles of the SOR that runs batches of iterations in one launch
+// (kernels_sor.hip), and its memory.
+struct SorControl;
+struct SorPlan {
+  bool ok = false;
+  int ty = 0, tz = 0, gy = 0, gz = 0;   // rows of a tile along y and z; tiles
+  double* tmp = nullptr;
+  unsigned long long* mail = nullptr;
+  double* part = nullptr;
+  SorControl* ctl = nullptr;
+};
+bool sor_plan(int nx, int ny, int nz, SorPlan& p);
+size_t sor_bytes(int nx, int ny, int nz);
 }  // namespace ek
 
 namespace ek {
@@ -143,6 +157,9 @@ struct ek_ctx {
   // already evaluated.
   ek_status sor_solve(const double* b, double* x, ek::PoissonScalars h, int& iters, double& res,
                       double& res0);
+  ek::SorPlan sor;
+  void sor_setup(char* mem);
+  bool sor_team_solve(const double* b, double* x, ek::PoissonScalars& h, int& it, ek_status& st);
   // With start_norms the start's residual has not been evaluated: the first
   // cycle does it (mg_start_in_cycle), before anything else of the cycle.
   ek_status mg_solve(const double* b, double* x, ek::PoissonScalars h, int& iters, double& res,

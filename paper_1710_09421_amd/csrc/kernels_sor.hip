@@ -1,0 +1,589 @@
+// Red-black SOR (Sec. II.C) of lattices that the chip's LDS holds: batches of
+// iterations in one launch, the potential kept in LDS and only the tiles' faces
+// exchanged.
+//
+// What bounds the iteration: a 64x64x128 lattice is 4 MB, so one launch per
+// half sweep and two per residual test are bound by their launches and by the
+// caches' latency (17 us an iteration, 22 with insulating walls).  Here
+// a workgroup owns a tile of whole x-rows (ty rows by tz planes) for a whole
+// batch; after each half sweep it sends the new values of its boundary rows to
+// its four neighbours and takes theirs, which costs about one trip through
+// the memory side of the chip per half sweep. Measured: 3.0 us an iteration
+// at 64x64x128 (256 tiles of 4 x 8 rows); a solve to 1e-8 from zero 6.93 ->
+// 1.62 ms, a step of the 48x48x64 insulating pore 16.6 -> 3.3 ms, a step of
+// the 32^3 box to 1e-10 1.76 -> 0.69 ms.
+//
+// Exchange: every value travels as one 64-bit device-scope store into a slot
+// of the sender's mailbox; the receiver polls the slot itself until it no
+// longer holds EMPTY (a NaN no arithmetic produces), then empties it again.
+// No flag follows the data and no fence is needed: a slot is one word, and
+// nothing else is read because of it.  Half sweep g uses slot set g & 3.  A
+// set is written again four half sweeps later, by when its reader has emptied
+// it: the reader's polling wait of half sweep g + 2 also waits for the stores
+// that emptied set g, and the sender cannot be at half sweep g + 4 before it
+// has received what the reader sent after that.  All values sent are taken
+// before a launch ends, so the mailboxes are empty between launches.
+//
+// The launch is cooperative, so every workgroup it waits for is resident; a
+// wait is bounded all the same (the solve then fails, and the context takes
+// the single launches from then on).
+//
+// Convergence: every tested iteration's sum of squared residuals costs no
+// reads of its own (at a colour-1 site from its update's neighbours and the
+// new value, at a colour-0 site from the next update's neighbours and the old
+// value).  The next launch begins with the verdict, which each of its
+// workgroups takes for itself from the same sums.  When an iteration inside
+// the batch met the tolerance, the batch is run again from its start for
+// exactly that many iterations, so the result is the iterate of the iteration
+// that converged, as with one test after another.  Otherwise the residual's
+// rate tells how long the next batch should be: it stops a little before the
+// expected end, and a short one then crosses it, so that little is run twice.
+#include <algorithm>
+#include <cmath>
+#include <cstdio>
+#include <cstring>
+
+#include "ek_context.h"
+#include "reduce.h"
+
+using namespace ek;
+
+namespace {
+
+constexpr unsigned long long EMPTY = 0xFFF7A5C35A3C7F11ull;
+constexpr int SLOTS = 4;
+constexpr int SOR_THREADS = 512;
+constexpr int SOR_WAVES = SOR_THREADS / 64;
+constexpr int SOR_MAX_BATCH = 64;
+constexpr int SOR_NEAR = 12;          // iterations left within which a batch crosses the end
+constexpr int SOR_SHORT = 4;          // else it stops this many before the expected end
+constexpr int SOR_MAX_ITEMS = 4;      // sites of a colour per thread
+constexpr int SOR_MAX_TAKE = 4;       // face values a thread takes per half sweep
+constexpr int SOR_MAX_GROUPS = 256;   // one workgroup per compute unit
+constexpr size_t SOR_LDS_MAX = 150 * 1024;
+constexpr int SOR_SPIN_LIMIT = 1 << 20;
+
+enum : int { SOR_START = 0, SOR_RAN = 1, SOR_REPLAYED = 2, SOR_FINAL = 3, SOR_LIMIT = 4 };
+
+}  // namespace
+
+// What the last launch of a solve left (device memory, two of them in turn).
+struct ek::SorControl {
+  int state;
+  int cur;            // RAN, REPLAYED: the buffer it started from (0 the caller's, 1 the
+                      // scratch one), its result is in the other; FINAL, LIMIT: the result
+  int base, n;        // iterations before it, and of it
+  int found;          // iteration that met the tolerance
+  int aborted;        // a wait ran into its limit
+  double omega;       // relaxation factor of its first half sweep
+  double omega_next;  // ... of the half sweep after it
+};
+
+namespace {
+
+struct SorArgs {
+  double* buf[2];
+  const double* b;
+  const uint32_t* mask;
+  const PoissonScalars* ps;
+  SorControl* ctl;    // [2]: read at launch & 1, written at the other
+  unsigned long long* mail;
+  double* part;       // [2][iteration of the batch][workgroup]: likewise
+  int launch;
+  int first;          // length of the first batch
+  int nx, ny, nz, ty, tz, gy, gz;
+  int max_iter, every;
+  double rj;
+  double tol;
+};
+
+__device__ __forceinline__ bool tested(const SorArgs& a, int it) {
+  return it % a.every == 0 || it == a.max_iter;
+}
+
+// What this launch runs, from what the last one left: base, n, cur and omega
+// of its batch, state = REPLAYED where the batch is the last one again (with
+// `found`), or FINAL / LIMIT and nothing to run.  `rel` is scratch.
+__device__ inline SorControl sor_verdict(const SorArgs& a, double* rel) {
+  SorControl c = a.ctl[a.launch & 1];
+  if (c.aborted) c.state = SOR_LIMIT;
+  if (c.state == SOR_START) {
+    c.state = SOR_RAN;
+    c.cur = c.base = 0;
+    c.n = a.first;
+    c.omega = 1.0;
+    return c;
+  }
+  if (c.state == SOR_REPLAYED) {
+    c.state = SOR_FINAL;
+    c.cur ^= 1;
+  }
+  if (c.state >= SOR_FINAL) return c;
+  const int W = gridDim.x, lane = threadIdx.x & 63;
+  const double* part = a.part + (size_t)(a.launch & 1) * SOR_MAX_BATCH * W;
+  const double b2 = a.ps->b2;
+  for (int it = 1 + (threadIdx.x >> 6); it <= c.n; it += SOR_WAVES) {
+    double s = 0.0;
+    if (tested(a, c.base + it))
+#pragma unroll 4
+      for (int k = lane; k < W; k += 64) s += part[(size_t)(it - 1) * W + k];
+    s = wave_sum(s);
+    if (lane == 0) rel[it - 1] = sqrt(s / b2);
+  }
+  __syncthreads();
+  int last = 0, before = 0;          // the last two tested iterations a quarter of it apart
+  for (int it = 1; it <= c.n; ++it) {
+    if (!tested(a, c.base + it)) continue;
+    if (rel[it - 1] <= a.tol) {
+      c.found = c.base + it;
+      if (it == c.n) {
+        c.state = SOR_FINAL;
+        c.cur ^= 1;
+      } else {
+        c.state = SOR_REPLAYED;
+        c.n = it;
+      }
+      return c;
+    }
+    last = it;
+    if (before == 0 || 4 * it <= 3 * c.n) before = it;
+  }
+  int n = SOR_MAX_BATCH;
+  if (last > before) {
+    const double rate = log(rel[last - 1] / rel[before - 1]) / (last - before);
+    const double left = log(a.tol / rel[last - 1]) / rate + (last - c.n);
+    if (rate < 0.0 && left < double(SOR_MAX_BATCH + SOR_SHORT)) {
+      const int k = max(1, int(ceil(left)));
+      n = k > SOR_NEAR ? k - SOR_SHORT : k + 2;
+    }
+  } else {
+    n = max(a.every, 8);
+  }
+  c.base += c.n;
+  c.n = min(min(n, SOR_MAX_BATCH), a.max_iter - c.base);
+  c.cur ^= 1;
+  c.omega = c.omega_next;
+  c.state = c.n > 0 ? SOR_RAN : SOR_LIMIT;
+  return c;
+}
+
+// NEU: insulating walls (fluid sites only, the link words' bits 1..6 mark the
+// solid face neighbours, see kernels_poisson.hip).  U: sites of a colour per
+// thread.
+template <bool NEU, int U>
+__global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
+  extern __shared__ double P[];      // [colour][row of the tile and its ring][x / 2]
+  __shared__ int s_abort;
+  __shared__ double s_rel[SOR_MAX_BATCH];
+  __shared__ double s_sum[SOR_WAVES];
+  const SorControl c = sor_verdict(a, s_rel);
+  if (c.state >= SOR_FINAL) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[(a.launch & 1) ^ 1] = c;
+    return;
+  }
+  const int n_it = c.n;
+  const int tid = threadIdx.x, w = blockIdx.x, W = gridDim.x;
+  const int ty = a.ty, tz = a.tz, hx = a.nx / 2, ry = ty + 2;
+  const int plane = ry * (tz + 2) * hx;
+  const int wy = w % a.gy, wz = w / a.gy, y0 = wy * ty, z0 = wz * tz;
+  const double* in = a.buf[c.cur];
+  double* out = a.buf[c.cur ^ 1];
+  const double shift = a.ps->shift;
+  if (tid == 0) s_abort = 0;
+  // the tile and its ring (the ring's corner rows are never read)
+  for (int t = tid; t < ry * (tz + 2) * a.nx; t += SOR_THREADS) {
+    const int row = t / a.nx, x = t - row * a.nx;
+    const int zz = row / ry - 1, yy = row % ry - 1;
+    const int y = (y0 + yy + a.ny) % a.ny, z = (z0 + zz + a.nz) % a.nz;
+    P[((x + y + z) & 1) * plane + row * hx + (x >> 1)] =
+        in[((long long)z * a.ny + y) * a.nx + x];
+  }
+  // this thread's sites: rows on the tile's faces first, so that what the
+  // neighbours wait for is sent before the inner rows are relaxed
+  const int rows = ty * tz, items = rows * hx;
+  const int ez = tz > 1 ? 2 : 1, ey = ty > 1 ? 2 : 1, mid = max(tz - 2, 0), inner = max(ty - 2, 0);
+  const int face_items = (ez * ty + mid * ey) * hx;
+  int own[U], yz[U], odd[U];         // LDS index; yy | zz << 16; x of colour 0 = 2 i + odd
+  double rhs[2][U];
+  int open[2][U];                    // NEU: bits 1..6 open neighbours, bit 0 fluid
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = min(tid + u * SOR_THREADS, items - 1);
+    int r = t / hx;
+    const int i = t - r * hx;
+    int yy, zz;
+    if (r < ez * ty) {
+      zz = r < ty ? 0 : tz - 1;
+      yy = r % ty;
+    } else if ((r -= ez * ty) < mid * ey) {
+      zz = 1 + r / ey;
+      yy = r % ey ? ty - 1 : 0;
+    } else {
+      r -= mid * ey;
+      zz = 1 + r / max(inner, 1);
+      yy = 1 + r % max(inner, 1);
+    }
+    own[u] = ((zz + 1) * ry + yy + 1) * hx + i;
+    yz[u] = yy | zz << 16;
+    odd[u] = (y0 + yy + z0 + zz) & 1;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int x = 2 * i + (odd[u] ^ k);
+      const long long s = ((long long)(z0 + zz) * a.ny + y0 + yy) * a.nx + x;
+      rhs[k][u] = a.b[s] + shift;
+      open[k][u] = 127;
+      if constexpr (NEU) {
+        const uint32_t m = a.mask[s];
+        open[k][u] = int(~m & 126u) | (m & MASK_SOLID ? 0 : 1);
+      }
+    }
+  }
+  // face values this thread takes: slot in the sender's mailbox, LDS target
+  const int face = 2 * (ty + tz) * hx;
+  int src[SOR_MAX_TAKE], dst[SOR_MAX_TAKE];
+  unsigned long long* send = a.mail + (size_t)w * face;
+  const size_t set = (size_t)W * face;
+#pragma unroll
+  for (int v = 0; v < SOR_MAX_TAKE; ++v) {
+    const int t = tid + v * SOR_THREADS;
+    src[v] = -1;
+    dst[v] = 0;
+    if (t >= face) continue;
+    int k = t / hx;
+    const int i = t - k * hx;
+    int from, row, slot;
+    if (k < tz) {                    // below in y: its face 1
+      from = wz * a.gy + (wy == 0 ? a.gy - 1 : wy - 1);
+      slot = (tz + k) * hx + i;
+      row = (k + 1) * ry;
+    } else if ((k -= tz) < tz) {     // above in y: its face 0
+      from = wz * a.gy + (wy == a.gy - 1 ? 0 : wy + 1);
+      slot = k * hx + i;
+      row = (k + 1) * ry + ty + 1;
+    } else if ((k -= tz) < ty) {     // below in z: its face 3
+      from = (wz == 0 ? a.gz - 1 : wz - 1) * a.gy + wy;
+      slot = (2 * tz + ty + k) * hx + i;
+      row = k + 1;
+    } else {                         // above in z: its face 2
+      k -= ty;
+      from = (wz == a.gz - 1 ? 0 : wz + 1) * a.gy + wy;
+      slot = (2 * tz + k) * hx + i;
+      row = (tz + 1) * ry + k + 1;
+    }
+    src[v] = from * face + slot;
+    dst[v] = row * hx + i;
+  }
+  // takes the values sent in half sweep g (colour g & 1) into the ring
+  auto take = [&](int g) {
+    unsigned long long* box = a.mail + (g & (SLOTS - 1)) * set;
+    unsigned long long v[SOR_MAX_TAKE];
+    int spins = 0;
+    bool all;
+    do {
+      all = true;
+#pragma unroll
+      for (int k = 0; k < SOR_MAX_TAKE; ++k) v[k] = 0;
+#pragma unroll
+      for (int k = 0; k < SOR_MAX_TAKE; ++k)
+        if (src[k] >= 0)
+          v[k] = __hip_atomic_load(box + src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int k = 0; k < SOR_MAX_TAKE; ++k) all = all && v[k] != EMPTY;
+      if (!all && ++spins > SOR_SPIN_LIMIT) {
+        s_abort = 1;
+        break;
+      }
+    } while (!all);
+#pragma unroll
+    for (int k = 0; k < SOR_MAX_TAKE; ++k)
+      if (src[k] >= 0) {
+        P[(g & 1) * plane + dst[k]] = __longlong_as_double((long long)v[k]);
+        __hip_atomic_store(box + src[k], EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+  };
+  const double rj = a.rj;
+  double omega = c.omega;
+  bool first = c.base == 0;
+  double acc = 0.0;
+  // sum over the face neighbours of site u of colour k (the other colour)
+  auto around = [&](int k, int u) -> double {
+    const double* q = P + (k ^ 1) * plane;
+    const int o = own[u], i = o % hx;
+    const bool right = (odd[u] ^ k) != 0;       // x = 2 i + 1
+    const double xm = q[right ? o : (i == 0 ? o + hx - 1 : o - 1)];
+    const double xp = q[right ? (i == hx - 1 ? o - hx + 1 : o + 1) : o];
+    const double ym = q[o - hx], yp = q[o + hx], zm = q[o - ry * hx], zp = q[o + ry * hx];
+    if constexpr (NEU) {
+      const int m = open[k][u];
+      double s = 0.0;
+      s += m & 2 ? xm : 0.0;
+      s += m & 4 ? xp : 0.0;
+      s += m & 8 ? ym : 0.0;
+      s += m & 16 ? yp : 0.0;
+      s += m & 32 ? zm : 0.0;
+      s += m & 64 ? zp : 0.0;
+      return s;
+    } else {
+      return xm + xp + ym + yp + zm + zp;
+    }
+  };
+  // squared residual at a site with neighbour sum s and value v
+  auto square = [&](int k, int u, double s, double v) {
+    const double d = NEU ? double(__builtin_popcount(open[k][u] & 126)) : 6.0;
+    const double lap = s - d * v;
+    const double r = rhs[k][u] - lap;
+    return r * r;
+  };
+  // the workgroup's sum of iteration it: by waves, and after the next barrier
+  // over the waves
+  auto sum_waves = [&] {
+    const double s = wave_sum(acc);
+    if ((tid & 63) == 0) s_sum[tid >> 6] = s;
+    acc = 0.0;
+  };
+  double* part = a.part + (size_t)((a.launch & 1) ^ 1) * SOR_MAX_BATCH * W;
+  auto store_part = [&](int it) {
+    if (tid == 0) {
+      double s = s_sum[0];
+      for (int k = 1; k < SOR_WAVES; ++k) s += s_sum[k];
+      part[(size_t)(it - 1) * W + w] = s;
+    }
+  };
+  auto give_up = [&] {
+    if (tid == 0)
+      for (int k = 0; k < 2; ++k)
+        __hip_atomic_store(&a.ctl[k].aborted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  for (int it = 1; it <= n_it; ++it) {
+    const bool test = tested(a, c.base + it), prev = it > 1 && tested(a, c.base + it - 1);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const int g = 2 * (it - 1) + k;
+      if (g > 0) take(g - 1);
+      __syncthreads();
+      if (s_abort) return give_up();
+      if (k == 1 && prev) store_part(it - 1);
+      unsigned long long* box = send + (g & (SLOTS - 1)) * set;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int t = tid + u * SOR_THREADS;
+        if (t >= items) continue;
+        double* p = P + k * plane + own[u];
+        const double old = *p;
+        double v = old;
+        if (!NEU || (open[k][u] & 1)) {
+          const double s = around(k, u);
+          if (k == 0 && prev) acc += square(k, u, s, old);
+          if constexpr (NEU)
+            v = old + omega * ((s - rhs[k][u]) / double(__builtin_popcount(open[k][u] & 126)) - old);
+          else
+            v = old + omega * ((s - rhs[k][u]) * (1.0 / 6.0) - old);
+          if (k == 1 && test) acc += square(k, u, s, v);
+          *p = v;
+        }
+        if (t < face_items) {
+          const int yy = yz[u] & 0xffff, zz = yz[u] >> 16, i = own[u] % hx;
+          unsigned long long m = (unsigned long long)__double_as_longlong(v);
+          if (m == EMPTY) m ^= 1;
+          auto put = [&](int slot) {
+            __hip_atomic_store(box + slot, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          };
+          if (yy == 0) put(zz * hx + i);
+          if (yy == ty - 1) put((tz + zz) * hx + i);
+          if (zz == 0) put((2 * tz + yy) * hx + i);
+          if (zz == tz - 1) put((2 * tz + ty + yy) * hx + i);
+        }
+      }
+      if (k == 0 && prev) sum_waves();
+      omega = first ? 1.0 / (1.0 - 0.5 * rj * rj) : 1.0 / (1.0 - 0.25 * rj * rj * omega);
+      first = false;
+    }
+  }
+  take(2 * n_it - 1);
+  __syncthreads();
+  if (s_abort) return give_up();
+  if (tested(a, c.base + n_it)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + u * SOR_THREADS < items && (!NEU || (open[0][u] & 1)))
+        acc += square(0, u, around(0, u), P[own[u]]);
+    sum_waves();
+    __syncthreads();
+    store_part(n_it);
+  }
+  for (int t = tid; t < rows * a.nx; t += SOR_THREADS) {
+    const int r = t / a.nx, x = t - r * a.nx;
+    const int zz = r / ty, yy = r - zz * ty, y = y0 + yy, z = z0 + zz;
+    out[((long long)z * a.ny + y) * a.nx + x] =
+        P[((x + y + z) & 1) * plane + ((zz + 1) * ry + yy + 1) * hx + (x >> 1)];
+  }
+  if (w == 0 && tid == 0) {
+    SorControl* o = a.ctl + ((a.launch & 1) ^ 1);
+    o->state = c.state;
+    o->cur = c.cur;
+    o->base = c.base;
+    o->n = c.n;
+    o->found = c.found;
+    o->omega = c.omega;
+    o->omega_next = omega;
+  }
+}
+
+__global__ void k_sor_reset(SorControl* c) {
+  if (threadIdx.x < 2) c[threadIdx.x] = SorControl{SOR_START, 0, 0, 0, 0, 0, 1.0, 1.0};
+}
+
+__global__ __launch_bounds__(256) void k_mail_empty(unsigned long long* mail, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) mail[i] = EMPTY;
+}
+
+size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
+
+size_t tile_lds(int nx, int ty, int tz) { return (size_t)(ty + 2) * (tz + 2) * nx * 8; }
+
+}  // namespace
+
+// The tile of whole x-rows: the most workgroups up to one per compute unit
+// (the shortest half sweep), and of equal counts the least face.
+bool ek::sor_plan(int nx, int ny, int nz, SorPlan& p) {
+  p = SorPlan{};
+  const int hx = nx / 2;
+  for (int ty = 1; ty <= ny; ++ty) {
+    if (ny % ty) continue;
+    for (int tz = 1; tz <= nz; ++tz) {
+      if (nz % tz) continue;
+      const int groups = (ny / ty) * (nz / tz);
+      const long long items = (long long)ty * tz * hx, face = 2LL * (ty + tz) * hx;
+      if (groups > SOR_MAX_GROUPS || items > (long long)SOR_MAX_ITEMS * SOR_THREADS ||
+          face > (long long)SOR_MAX_TAKE * SOR_THREADS || tile_lds(nx, ty, tz) > SOR_LDS_MAX)
+        continue;
+      const int best = p.gy * p.gz;
+      if (groups > best || (groups == best && ty + tz < p.ty + p.tz)) {
+        p.ty = ty;
+        p.tz = tz;
+        p.gy = ny / ty;
+        p.gz = nz / tz;
+      }
+    }
+  }
+  return p.ty > 0;
+}
+
+size_t ek::sor_bytes(int nx, int ny, int nz) {
+  SorPlan p;
+  if (!sor_plan(nx, ny, nz, p)) return 0;
+  const size_t groups = (size_t)p.gy * p.gz, face = 2 * (size_t)(p.ty + p.tz) * (nx / 2);
+  return al256((size_t)nx * ny * nz * 8) + al256(SLOTS * groups * face * 8) +
+         al256((size_t)2 * SOR_MAX_BATCH * groups * 8) + 256;
+}
+
+void ek_ctx::sor_setup(char* mem) {
+  if (!sor_plan(p.nx, p.ny, p.nz, sor)) return;
+  const size_t groups = (size_t)sor.gy * sor.gz;
+  const size_t slots = SLOTS * groups * 2 * (size_t)(sor.ty + sor.tz) * (p.nx / 2);
+  sor.tmp = (double*)mem;
+  mem += al256((size_t)dims.n * 8);
+  sor.mail = (unsigned long long*)mem;
+  mem += al256(slots * 8);
+  sor.part = (double*)mem;
+  mem += al256((size_t)2 * SOR_MAX_BATCH * groups * 8);
+  sor.ctl = (SorControl*)mem;
+  hipLaunchKernelGGL(k_mail_empty, dim3(int((slots + 255) / 256)), dim3(256), 0, stream, sor.mail,
+                     slots);
+  sor.ok = true;
+}
+
+// The solve of sor_solve by batches in one launch each; false (and x as it
+// was) where that is not possible here.
+bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int& it, ek_status& st) {
+  st = EK_OK;
+  if (!sor.ok) return false;
+  SorArgs a{};
+  a.buf[0] = x;
+  a.buf[1] = sor.tmp;
+  a.b = bb;
+  a.mask = mask;
+  a.ps = ps;
+  a.ctl = sor.ctl;
+  a.mail = sor.mail;
+  a.part = sor.part;
+  a.nx = p.nx;
+  a.ny = p.ny;
+  a.nz = p.nz;
+  a.ty = sor.ty;
+  a.tz = sor.tz;
+  a.gy = sor.gy;
+  a.gz = sor.gz;
+  a.max_iter = p.poisson_max_iter;
+  a.every = p.poisson_check_every;
+  a.rj = jacobi_radius();
+  a.tol = p.poisson_tol;
+  const int groups = sor.gy * sor.gz, items = sor.ty * sor.tz * (p.nx / 2);
+  const size_t lds = tile_lds(p.nx, sor.ty, sor.tz);
+  auto launch = [&](auto kernel) -> bool {
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    void* args[] = {(void*)&a};
+    if (hipLaunchCooperativeKernel((const void*)kernel, dim3(groups), dim3(SOR_THREADS), args,
+                                   (unsigned)lds, stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    return true;
+  };
+  const int u = (items + SOR_THREADS - 1) / SOR_THREADS;
+  auto run = [&]() -> bool {
+    if (insulating())
+      return u == 1 ? launch(k_sor_team<true, 1>) : u == 2 ? launch(k_sor_team<true, 2>)
+                                                           : launch(k_sor_team<true, 4>);
+    return u == 1 ? launch(k_sor_team<false, 1>) : u == 2 ? launch(k_sor_team<false, 2>)
+                                                          : launch(k_sor_team<false, 4>);
+  };
+  hipLaunchKernelGGL(k_sor_reset, dim3(1), dim3(64), 0, stream, sor.ctl);
+  SorControl c{};
+  // full batches, the two that end the solve, its second run and the verdict
+  // on that (a launch with nothing left to run ends at once)
+  const int expect = last_iters > 0 ? last_iters : 200;
+  a.first = std::min({expect > SOR_NEAR ? expect - SOR_SHORT : expect + 2, SOR_MAX_BATCH,
+                      p.poisson_max_iter});
+  int ahead = expect / SOR_MAX_BATCH + 4;
+  while (c.state < SOR_FINAL && !c.aborted) {
+    for (int k = 0; k < ahead; ++k, ++a.launch)
+      if (!run()) {
+        sor.ok = false;
+        if (a.launch == 0) return false;
+        st = fail(EK_EHIP, "a cooperative launch of the SOR iterations was refused");
+        return true;
+      }
+    ahead = 2;
+    if (hipMemcpyAsync(pinned, sor.ctl + (a.launch & 1), sizeof c, hipMemcpyDeviceToHost, stream) !=
+        hipSuccess) {
+      st = fail(EK_EHIP, "reading the solve's state failed");
+      return true;
+    }
+    st = sync();
+    if (st) return true;
+    std::memcpy(&c, pinned, sizeof c);
+  }
+  if (c.aborted) {
+    sor.ok = false;   // the mailboxes are no longer empty: single launches from now on
+    st = fail(EK_EHIP, "a workgroup of the SOR iterations waited beyond its limit");
+    return true;
+  }
+  if (c.cur == 1 &&
+      hipMemcpyAsync(x, sor.tmp, dims.n * 8, hipMemcpyDeviceToDevice, stream) != hipSuccess) {
+    st = fail(EK_EHIP, "copying the iterate failed");
+    return true;
+  }
+  // the residual of the result as the single launches take it
+  it = c.state == SOR_FINAL ? c.found : c.base;
+  const int nr = residual_launch(bb, x);
+  launch_residual_final(partials, nr, p.poisson_tol, it, 0, ps, stream);
+  st = read_scalars(&h);
+  return true;
+}
