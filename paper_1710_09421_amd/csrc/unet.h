@@ -65,12 +65,15 @@ struct UNet {
   hipStream_t stream = nullptr;
 
   // forward activations
-  uint16_t *x0 = nullptr, *a1 = nullptr, *p1 = nullptr, *a2 = nullptr, *p2 = nullptr;
+  // (x0, c2 and c1 are kept only for the backward pass)
+  uint32_t* x0 = nullptr;     // the two input channels
+  uint16_t *a1 = nullptr, *p1 = nullptr, *a2 = nullptr, *p2 = nullptr;
   uint16_t *a3 = nullptr, *u3 = nullptr, *c2 = nullptr, *u2 = nullptr, *c1 = nullptr;
   float* out = nullptr;
   // backward
-  uint16_t *d0 = nullptr, *g1 = nullptr, *du2 = nullptr, *g2 = nullptr, *du3 = nullptr;
-  uint16_t *g3 = nullptr, *dp2 = nullptr, *gb = nullptr, *dp1 = nullptr, *ga = nullptr;
+  uint32_t* d0 = nullptr;     // the loss gradient, a pair with 0
+  uint16_t *g1 = nullptr, *du2 = nullptr, *g2 = nullptr, *du3 = nullptr;
+  uint16_t *g3 = nullptr, *dp2 = nullptr, *gb = nullptr, *dp1 = nullptr;
   float* wpart = nullptr;
   // parameters
   float *params = nullptr, *grad = nullptr, *adam_m = nullptr, *adam_v = nullptr;
