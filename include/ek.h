@@ -482,16 +482,17 @@ ek_status ek_unet_read_loss(ek_unet* net, double* mean_loss, int64_t* count);
 
 /* ---------------------------------------------------------------------------
  * Ensemble: uneven replicas of one geometry (translocation replicas with their
- * own salt noise, applied field and chain, Sec. IV.A) advanced together by ONE
- * persistent kernel launch per ek_ensemble_step call: a team of 1, 2 or 4
- * workgroups per replica runs the whole time loop of Fig. 1 for that replica
- * (charge pass, multigrid Poisson solve with its own convergence test, chain
- * substeps, fused lattice step), so replicas with more Poisson cycles or
- * longer chains never hold the others back.  The Poisson method is
- * multigrid, started from the previous solution, or from the extrapolated
- * one when the base warm_start is EK_WS_EXTRAP (other values: the previous
- * solution); all other parameters come from the base ek_params except the
- * applied field.
+ * own salt noise, applied field and chain, Sec. IV.A) advanced together.  Each
+ * launch of a step (charge pass, direct Poisson solve as EK_POISSON_MG's time
+ * loop, chain, fused lattice step) covers all replicas; the host enqueues the
+ * steps of a call and then looks at the replicas, each of which has its own
+ * convergence test.  Boxes without a direct solver (an odd side or one beyond
+ * 960) and a poisson_max_iter below 20 take one persistent launch per
+ * call instead, in which a team of 1, 2 or 4 workgroups per replica runs the
+ * whole time loop of Fig. 1 with multigrid cycles.  The solves start from the
+ * previous solution, or from the extrapolated one when the base warm_start is
+ * EK_WS_EXTRAP (other values: the previous solution); all other parameters
+ * come from the base ek_params except the applied field.
  * ------------------------------------------------------------------------- */
 typedef struct ek_ensemble ek_ensemble;
 
@@ -523,8 +524,7 @@ ek_status ek_ensemble_set_replica(ek_ensemble* ens, int32_t r, const double* E_e
                                   const double* vel, const double* charge,
                                   const ek_polymer_params* pp);
 
-/* n_steps steps of every replica in one persistent launch; returns after the
- * stream is synchronised.  EK_ENOCONV if a replica's Poisson solve did not
+/* n_steps steps of every replica; returns after the stream is synchronised.  EK_ENOCONV if a replica's Poisson solve did not
  * reach the tolerance in poisson_max_iter cycles, EK_EUNSTABLE if a replica's
  * mass became non-finite or its chain failed (ek_ensemble_last_error names
  * the replica). */
@@ -536,10 +536,11 @@ ek_status ek_ensemble_get_potential(ek_ensemble* ens, int32_t r, double* psi);
 ek_status ek_ensemble_get_beads(ek_ensemble* ens, int32_t r, double* pos, double* vel);
 ek_status ek_ensemble_get_stats(ek_ensemble* ens, int32_t r, ek_stats* out);
 
-/* Time spent by replica r's team in the phases of every step it has taken
- * since the ensemble was created (the persistent kernel's own clock:
- * thread 0 of the team's first workgroup reads the device wall clock at the
- * team barriers that end the phases), in milliseconds: ms[0] the bead deposit
+/* Time spent in the phases of every step replica r has taken since the
+ * ensemble was created (device wall clock, read at the end of each phase by a
+ * kernel of the replica's own or, in the persistent kernel, by its team at
+ * the barriers; the phases of launched steps are those of all replicas
+ * together), in milliseconds: ms[0] the bead deposit
  * and charge pass (Eq. poisson's right-hand side), ms[1] the Poisson solve
  * and gauge, ms[2] the chain (Sec. II.B), ms[3] the fused collide-and-stream
  * (Eq. kernelf2) with its sums.  Host array of 4; reads the values as of the
@@ -547,7 +548,8 @@ ek_status ek_ensemble_get_stats(ek_ensemble* ens, int32_t r, ek_stats* out);
  * NULL ms; EK_EHIP when the device reports no wall-clock rate. */
 ek_status ek_ensemble_phase_times(ek_ensemble* ens, int32_t r, double* ms);
 
-/* Workgroup size of the persistent kernel (256, 512 or 1024). */
+/* Workgroup size of the persistent kernel (256, 512 or 1024; launched steps
+ * have shapes of their own). */
 ek_status ek_ensemble_set_threads(ek_ensemble* ens, int32_t threads);
 
 /* Workgroups per replica (1, 2 or 4).  With more than one, the replica's

@@ -296,7 +296,8 @@ ek_status ek_ctx::poisson(const double* bb, double* x, bool learned, int& iters,
   last_consulted = 0;
   // the time loop solves directly where the sides have a plan; a stand-alone
   // solve keeps the multigrid cycles, whose number its callers compare starts by
-  const bool direct = p.poisson_method == EK_POISSON_MG && spec.ok && !solo;
+  const bool direct = p.poisson_method == EK_POISSON_MG && spec.ok && !solo &&
+                      p.poisson_max_iter >= DIRECT_MIN_CYCLES;
   if (!learned && direct) return spectral_solve(bb, x, h, iters, res, res0, true);
   if (!learned && p.poisson_method == EK_POISSON_MG) {
     // the start's residual stays on the device (the cycles test its flag and

@@ -1,6 +1,7 @@
-// Ensemble of uneven replicas in one persistent launch.
+// Ensemble of uneven replicas: the host side, and the persistent kernel that
+// takes the ensembles which the launched steps (kernels_replicas.hip) do not.
 //
-// One workgroup owns one replica for the whole call: it runs every phase of
+// In the persistent launch one workgroup owns one replica for the whole call: it runs every phase of
 // the time step (Fig. 1) on its replica with __syncthreads as the only
 // barrier — bead charge deposit, charge pass, multigrid Poisson solve with the
 // replica's own convergence test, bead boxes and chain substeps, fused
@@ -20,6 +21,7 @@
 #include <vector>
 
 #include "ek_context.h"
+#include "ensemble.h"
 #include "lb_site.h"
 #include "md_chain.h"
 #include "mg_site.h"
@@ -28,8 +30,6 @@ using namespace ek;
 
 namespace {
 
-constexpr int ENS_TABLE_BITS = 12;     // node table of a replica: 4096 slots
-constexpr int ENS_MAX_BEADS = 64;      // node sums of a chain live in LDS
 constexpr int ENS_COARSEST_CAP = 200;
 // smoothing sweeps of the in-kernel V-cycle: V(1,2), as the launched solver
 // (with the extrapolated start 6.3 against 6.6 ms per step of 64 replicas for
@@ -40,53 +40,10 @@ constexpr int ENS_NU1 = 1, ENS_NU2 = 2;
 // at 1.15 and 7.21 at 1.3 (the first 23 steps from the extrapolated start).
 constexpr double ENS_OMEGA_FINEST = 1.2;
 
-enum : int { ST_OK = 0, ST_NOCONV = 1, ST_UNSTABLE = 2, ST_TIMEOUT = 3 };
-
 // A replica is advanced by a team of G workgroups (G = 1, 2 or 4) of one
 // cooperative launch: the site-parallel phases on the finest level are split
 // over the team, the coarse multigrid levels and the chain run in member 0.
-constexpr int ENS_MAX_GROUP = 4;
 constexpr long long ENS_SPIN_LIMIT = 1ll << 24;   // ~1 s of s_sleep: then the team aborts
-
-// Team barrier state and reduction partials of one replica (global memory,
-// cleared by the host before every launch).  Partials are double-buffered by
-// the parity of the reduction count, so a member that has summed reduction k
-// can write reduction k + 1 while the others still read k.
-struct TeamSync {
-  int count;                  // barrier arrivals
-  int abort;                  // set when a member waited beyond the spin limit
-  int pad[14];
-  double part[2][ENS_MAX_GROUP][8];
-};
-
-// Per-replica device pointers and parameters.
-struct RepDev {
-  void* f[2];                 // populations; f[cur] holds the current ones
-  TeamSync* sync;
-  uint32_t* mask;             // link words (own copy: the bead flag is per replica)
-  double* psi;
-  double* psi_old;            // psi(t-2) for the extrapolated start, or null
-  int psi_hist;               // previous solutions held (0, 1 or 2)
-  double* b;
-  double* mg;                 // multigrid levels 1.. (x then f per level)
-  int* keys;
-  long long* vals;
-  BeadState bs;
-  MDParams mp;
-  LBParams lp;
-  int n_beads;
-  int cur;
-  int status;
-  int steps;                  // steps completed
-  int last_cycles;
-  double last_res;
-  double last_res0;
-  double stats[6];            // species masses and fluid momentum of f(t)
-  // wall-clock ticks spent by the team's first workgroup in the phases of
-  // all steps so far: charge pass, Poisson solve, chain, collide-and-stream
-  unsigned long long phase_ticks[4];
-  unsigned long long phase_mark;   // clock at the start of the current phase
-};
 
 struct EnsConst {
   Dims d;
@@ -465,6 +422,7 @@ struct ek_ensemble {
   int threads = 512;
   int group = 1;              // workgroups per replica
   double wall_khz = 0.0;      // rate of the device's wall clock
+  RepBatch batch;             // launched steps (batch.spec.ok: the box has them)
   std::string err;
 
   ek_status fail(ek_status st, const std::string& m) {
@@ -516,6 +474,8 @@ BeadState carve_beads(char* mem, int maxb) {
   return s;
 }
 
+// Device bytes before the replicas' own: descriptors, wall charge and the
+// launched steps' tables.
 size_t shared_bytes(int n_rep) { return al256(sizeof(RepDev) * (size_t)n_rep) + 256; }
 
 ek_status check(const ek_params* p, int n_rep, int max_beads, std::string& why) {
@@ -602,14 +562,71 @@ ek_status download(ek_ensemble* e) {
   return EK_OK;
 }
 
-ek_status run_steps(ek_ensemble* e, int n_steps, int threads, int group) {
-  if (n_steps == 0) return EK_OK;
+// n_steps steps of every replica as launches over all of them.  The host
+// looks at the replicas once all steps are enqueued; one whose solve missed
+// the tolerance after its first cycle has paused there, gets its further
+// cycles with a look after each, and takes its remaining steps in another turn.
+ek_status run_launched(ek_ensemble* e, int n_steps) {
+  RepBatch& b = e->batch;
+  b.beads = 0;
+  for (RepDev& R : e->reps) {
+    R.todo = n_steps;
+    b.beads = std::max(b.beads, R.n_beads);
+  }
   ek_status st = upload(e);
   if (st) return st;
-  st = e->p.precision == EK_FP64 ? launch_ensemble<double>(e, n_steps, threads, group)
-                                 : launch_ensemble<float>(e, n_steps, threads, group);
+  auto launched = [&](hipError_t err) -> ek_status {
+    return err == hipSuccess ? EK_OK
+                             : e->fail(EK_EHIP, std::string("ensemble launch failed: ") + hipGetErrorString(err));
+  };
+  st = launched(replicas_begin(b, e->stream));
   if (st) return st;
-  st = download(e);
+  for (;;) {
+    int left = 0;
+    for (const RepDev& R : e->reps)
+      if (R.status == ST_OK) left = std::max(left, R.todo);
+    if (left == 0) return EK_OK;
+    for (int t = 0; t < left && !st; ++t) st = launched(replicas_step(b, e->stream));
+    if (!st) st = download(e);
+    if (st) return st;
+    for (;;) {   // the paused ones: cycles until each meets the tolerance or runs out of them
+      bool paused = false, more = false;
+      for (RepDev& R : e->reps) {
+        if (R.status != ST_PAUSED) continue;
+        if (!(R.last_res > e->p.poisson_tol)) paused = true;
+        else if (R.last_cycles < e->p.poisson_max_iter) paused = more = true;
+        else R.status = ST_NOCONV;
+      }
+      st = upload(e);
+      if (st) return st;
+      if (!paused) break;
+      st = launched(more ? replicas_cycle(b, e->stream) : replicas_finish(b, e->stream));
+      if (!st) st = download(e);
+      if (st) return st;
+    }
+  }
+}
+
+// Launches over all replicas with the direct solve where the box has one;
+// else the persistent kernel (64 replicas of 48x48x96: 5.9 ms per step, 3.8
+// of them multigrid).
+bool launched_path(const ek_ensemble* e) {
+  return e->batch.spec.ok && e->p.poisson_max_iter >= DIRECT_MIN_CYCLES &&
+         e->p.precision == EK_FP32;
+}
+
+ek_status run_steps(ek_ensemble* e, int n_steps, int threads, int group) {
+  if (n_steps == 0) return EK_OK;
+  ek_status st;
+  if (launched_path(e)) {
+    st = run_launched(e, n_steps);
+  } else {
+    st = upload(e);
+    if (st) return st;
+    st = e->p.precision == EK_FP64 ? launch_ensemble<double>(e, n_steps, threads, group)
+                                   : launch_ensemble<float>(e, n_steps, threads, group);
+    if (!st) st = download(e);
+  }
   if (st) return st;
   for (int r = 0; r < e->n_rep; ++r) {
     const RepDev& R = e->reps[r];
@@ -643,7 +660,9 @@ ek_status ek_ensemble_workspace_bytes(const ek_params* base, int32_t n_rep, int3
     return EK_EINVAL;
   }
   const size_t n = (size_t)base->nx * base->ny * base->nz;
-  *bytes = shared_bytes(n_rep) + al256(n * 8) + (size_t)n_rep * rep_layout(base, max_beads).total;
+  *bytes = shared_bytes(n_rep) + al256(n * 8) +
+           replicas_bytes(base->nx, base->ny, base->nz, n_rep) +
+           (size_t)n_rep * rep_layout(base, max_beads).total;
   return EK_OK;
 }
 
@@ -684,7 +703,8 @@ ek_status ek_ensemble_create(const ek_params* base, int32_t n_rep, int32_t max_b
   e->wall_q = (double*)(ws + shared_bytes(n_rep));
   const RepLayout RL = rep_layout(base, max_beads);
   e->rep_bytes = RL.total;
-  char* base_rep = ws + shared_bytes(n_rep) + al256(e->d.n * 8);
+  char* batch_mem = ws + shared_bytes(n_rep) + al256(e->d.n * 8);
+  char* base_rep = batch_mem + replicas_bytes(base->nx, base->ny, base->nz, n_rep);
   // multigrid hierarchy (same construction as the single-system solver)
   EnsConst& ec = e->ec;
   ec.d = e->d;
@@ -723,6 +743,12 @@ ek_status ek_ensemble_create(const ek_params* base, int32_t n_rep, int32_t max_b
     }
   }
   ec.lds_bits = lds_bits_for(max_beads);
+  RepBatch& bt = e->batch;
+  replicas_setup(bt, batch_mem, base->nx, base->ny, base->nz, n_rep);
+  bt.reps = e->reps_dev;
+  bt.wall_q = e->wall_q;
+  bt.inv_eps = ec.inv_eps;
+  bt.tol = ec.tol;
   e->reps.resize(n_rep);
   e->have_replica.assign(n_rep, false);
   for (int r = 0; r < n_rep; ++r) {

@@ -45,11 +45,12 @@ struct SpecArgs {
   const double *lx, *ly, *lz;
   double* hat;
   double h2, inv_n;
+  const SpecItem* items;       // several problems: this block's is items[blockIdx.y]
 };
 
-SpecArgs args_of(const Spectral& s) {
+SpecArgs args_of(const Spectral& s, const SpecItem* items) {
   return SpecArgs{s.nx, s.ny, s.nz, s.px, s.py, s.pz, s.tx, s.ty, s.tz, s.lx, s.ly, s.lz, s.hat,
-                  s.h2, 1.0 / (double(s.nx) * s.ny * s.nz)};
+                  s.h2, 1.0 / (double(s.nx) * s.ny * s.nz), items};
 }
 
 // Workgroup -> item, so that each XCD (which takes every eighth workgroup)
@@ -98,6 +99,10 @@ __global__ __launch_bounds__(MAXT) void k_spec_plane(const double* __restrict__ 
                                                      const PoissonScalars* __restrict__ ps,
                                                      double* __restrict__ partials, SpecArgs a) {
   extern __shared__ __align__(16) double D[];
+  if (a.items) {
+    const SpecItem& it = a.items[blockIdx.y];
+    x = it.x; f = it.f; ps = it.ps; partials = it.partials; a.hat = it.hat;
+  }
   if (ps->done) return;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int z = xcd_order(blockIdx.x, gridDim.x), ld = a.nx + 1;
@@ -137,7 +142,12 @@ __global__ __launch_bounds__(MAXT) void k_spec_plane_back(double* __restrict__ x
                                                           const PoissonScalars* __restrict__ ps,
                                                           SpecArgs a) {
   extern __shared__ __align__(16) double D[];
+  if (a.items) {
+    const SpecItem& it = a.items[blockIdx.y];
+    x = it.x; ps = it.ps; a.hat = it.hat;
+  }
   if (ps->done) return;
+  const double gauge = a.items ? ps->psum * a.inv_n : 0.0;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int z = xcd_order(blockIdx.x, gridDim.x), ld = a.nx + 1;
   double2* twx = (double2*)(D + (((size_t)a.ny * ld + 1) & ~size_t(1)));
@@ -166,7 +176,7 @@ __global__ __launch_bounds__(MAXT) void k_spec_plane_back(double* __restrict__ x
     int ix;
     const int iy = divide(t, a.nx, inv_nx, ix);
     const double v = D[iy * ld + ix];
-    out[t] = ADD ? out[t] + v : v;
+    out[t] = ADD ? out[t] + (v - gauge) : v;
   }
 }
 
@@ -177,6 +187,10 @@ __global__ __launch_bounds__(MAXT) void k_spec_rows(const double* __restrict__ x
                                                     const PoissonScalars* __restrict__ ps,
                                                     double* __restrict__ partials, SpecArgs a) {
   extern __shared__ __align__(16) double D[];
+  if (a.items) {
+    const SpecItem& it = a.items[blockIdx.y];
+    x = it.x; f = it.f; ps = it.ps; partials = it.partials; a.hat = it.hat;
+  }
   if (ps->done) return;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int nty = (a.ny + TILE - 1) / TILE;
@@ -211,7 +225,12 @@ __global__ __launch_bounds__(MAXT) void k_spec_rows_back(double* __restrict__ x,
                                                          const PoissonScalars* __restrict__ ps,
                                                          SpecArgs a) {
   extern __shared__ __align__(16) double D[];
+  if (a.items) {
+    const SpecItem& it = a.items[blockIdx.y];
+    x = it.x; ps = it.ps; a.hat = it.hat;
+  }
   if (ps->done) return;
+  const double gauge = a.items ? ps->psum * a.inv_n : 0.0;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int nty = (a.ny + TILE - 1) / TILE;
   const int b = xcd_order(blockIdx.x, gridDim.x), z = b / nty, y0 = (b - z * nty) * TILE;
@@ -235,7 +254,7 @@ __global__ __launch_bounds__(MAXT) void k_spec_rows_back(double* __restrict__ x,
     int ix;
     const int j = divide(t, a.nx, inv_nx, ix);
     const double v = D[j * ld + ix];
-    x[first + t] = ADD ? x[first + t] + v : v;
+    x[first + t] = ADD ? x[first + t] + (v - gauge) : v;
   }
 }
 
@@ -246,6 +265,10 @@ template <int EPT, int MAXT, bool PRIME, bool Z>
 __global__ __launch_bounds__(MAXT) void k_spec_cols(const PoissonScalars* __restrict__ ps,
                                                     SpecArgs a) {
   extern __shared__ __align__(16) double D[];
+  if (a.items) {
+    const SpecItem& it = a.items[blockIdx.y];
+    ps = it.ps; a.hat = it.hat;
+  }
   if (ps->done) return;
   const int tid = threadIdx.x, nthr = blockDim.x;
   const int ntx = (a.nx + TILE - 1) / TILE;
@@ -375,20 +398,26 @@ bool ek::dht_plan(int n, DhtPlan& plan) {
   return true;
 }
 
-size_t ek::spectral_bytes(int nx, int ny, int nz) {
+size_t ek::spectral_table_bytes(int nx, int ny, int nz) {
   DhtPlan p;
   if (!dht_plan(nx, p) || !dht_plan(ny, p) || !dht_plan(nz, p)) return 0;
-  return al256((size_t)nx * ny * nz * 8) + al256((size_t)(nx + ny + nz) * 24) + 256;
+  return al256((size_t)(nx + ny + nz) * 24);
 }
 
-void ek::spectral_setup(Spectral& s, char* mem, int nx, int ny, int nz, double h2) {
+size_t ek::spectral_bytes(int nx, int ny, int nz) {
+  const size_t tables = spectral_table_bytes(nx, ny, nz);
+  return tables ? al256((size_t)nx * ny * nz * 8) + tables + 256 : 0;
+}
+
+void ek::spectral_setup(Spectral& s, char* mem, int nx, int ny, int nz, double h2,
+                        bool own_field) {
   s = Spectral{};
   if (!dht_plan(nx, s.px) || !dht_plan(ny, s.py) || !dht_plan(nz, s.pz)) return;
   s.nx = nx;
   s.ny = ny;
   s.nz = nz;
   s.h2 = h2;
-  s.hat = (double*)mem;
+  s.hat = own_field ? (double*)mem : nullptr;
   const int m = nx + ny + nz;
   std::vector<double> host((size_t)3 * m);
   double* lam = host.data() + 2 * (size_t)m;
@@ -404,7 +433,7 @@ void ek::spectral_setup(Spectral& s, char* mem, int nx, int ny, int nz, double h
       const double h = std::sin(M_PI * kk / n);
       lam[at] = -4.0 * h * h;
     }
-  char* tab = mem + al256((size_t)nx * ny * nz * 8);
+  char* tab = mem + (own_field ? al256((size_t)nx * ny * nz * 8) : 0);
   if (hipMemcpy(tab, host.data(), host.size() * 8, hipMemcpyHostToDevice) != hipSuccess) {
     (void)hipGetLastError();
     return;
@@ -470,19 +499,21 @@ int ek::spectral_blocks(const Spectral& s) {
 }
 
 int ek::launch_spectral_forward(const Spectral& s, const double* x, const double* f,
-                                const PoissonScalars* ps, double* partials, hipStream_t st) {
-  const SpecArgs a = args_of(s);
+                                const PoissonScalars* ps, double* partials, hipStream_t st,
+                                const SpecItem* items, int count) {
+  const SpecArgs a = args_of(s, items);
   const int nb = spectral_blocks(s);
+  const bool res = x || items;
   if (s.plane_shape >= 0) {
     with_shape(s.plane_shape, s.plane_prime, [&](auto e, auto t, auto pr) {
       constexpr int E = decltype(e)::value, T = decltype(t)::value;
       constexpr bool P = decltype(pr)::value;
       const size_t lds = plane_lds(s.nx, s.ny);
-      if (x)
-        hipLaunchKernelGGL((k_spec_plane<E, T, P, true>), dim3(nb), dim3(T), lds, st, x, f, ps,
+      if (res)
+        hipLaunchKernelGGL((k_spec_plane<E, T, P, true>), dim3(nb, count), dim3(T), lds, st, x, f, ps,
                            partials, a);
       else
-        hipLaunchKernelGGL((k_spec_plane<E, T, P, false>), dim3(nb), dim3(T), lds, st, x, f, ps,
+        hipLaunchKernelGGL((k_spec_plane<E, T, P, false>), dim3(nb, count), dim3(T), lds, st, x, f, ps,
                            partials, a);
     });
     return nb;
@@ -491,23 +522,23 @@ int ek::launch_spectral_forward(const Spectral& s, const double* x, const double
     constexpr int E = decltype(e)::value, T = decltype(t)::value;
     constexpr bool P = decltype(pr)::value;
     const size_t lds = rows_lds(s.nx);
-    if (x)
-      hipLaunchKernelGGL((k_spec_rows<E, T, P, true>), dim3(nb), dim3(T), lds, st, x, f, ps, partials, a);
+    if (res)
+      hipLaunchKernelGGL((k_spec_rows<E, T, P, true>), dim3(nb, count), dim3(T), lds, st, x, f, ps, partials, a);
     else
-      hipLaunchKernelGGL((k_spec_rows<E, T, P, false>), dim3(nb), dim3(T), lds, st, x, f, ps, partials, a);
+      hipLaunchKernelGGL((k_spec_rows<E, T, P, false>), dim3(nb, count), dim3(T), lds, st, x, f, ps, partials, a);
   });
   return nb;
 }
 
 void ek::launch_spectral_solve(const Spectral& s, double* x, bool add, const PoissonScalars* ps,
-                               hipStream_t st) {
-  const SpecArgs a = args_of(s);
+                               hipStream_t st, const SpecItem* items, int count) {
+  const SpecArgs a = args_of(s, items);
   const int nb = spectral_blocks(s), ntx = (s.nx + TILE - 1) / TILE;
   auto along_y = [&] {
     with_shape(s.col_shape, s.col_prime, [&](auto e, auto t, auto pr) {
       constexpr int E = decltype(e)::value, T = decltype(t)::value;
       constexpr bool P = decltype(pr)::value;
-      hipLaunchKernelGGL((k_spec_cols<E, T, P, false>), dim3(ntx * s.nz), dim3(T), cols_lds(s.ny), st,
+      hipLaunchKernelGGL((k_spec_cols<E, T, P, false>), dim3(ntx * s.nz, count), dim3(T), cols_lds(s.ny), st,
                          ps, a);
     });
   };
@@ -515,7 +546,7 @@ void ek::launch_spectral_solve(const Spectral& s, double* x, bool add, const Poi
   with_shape(s.z_shape, s.z_prime, [&](auto e, auto t, auto pr) {
     constexpr int E = decltype(e)::value, T = decltype(t)::value;
     constexpr bool P = decltype(pr)::value;
-    hipLaunchKernelGGL((k_spec_cols<E, T, P, true>), dim3(ntx * s.ny), dim3(T), cols_lds(s.nz), st, ps,
+    hipLaunchKernelGGL((k_spec_cols<E, T, P, true>), dim3(ntx * s.ny, count), dim3(T), cols_lds(s.nz), st, ps,
                        a);
   });
   if (s.plane_shape < 0) along_y();
@@ -525,9 +556,9 @@ void ek::launch_spectral_solve(const Spectral& s, double* x, bool add, const Poi
       constexpr bool P = decltype(pr)::value;
       const size_t lds = plane_lds(s.nx, s.ny);
       if (add)
-        hipLaunchKernelGGL((k_spec_plane_back<E, T, P, true>), dim3(nb), dim3(T), lds, st, x, ps, a);
+        hipLaunchKernelGGL((k_spec_plane_back<E, T, P, true>), dim3(nb, count), dim3(T), lds, st, x, ps, a);
       else
-        hipLaunchKernelGGL((k_spec_plane_back<E, T, P, false>), dim3(nb), dim3(T), lds, st, x, ps, a);
+        hipLaunchKernelGGL((k_spec_plane_back<E, T, P, false>), dim3(nb, count), dim3(T), lds, st, x, ps, a);
     });
     return;
   }
@@ -536,9 +567,9 @@ void ek::launch_spectral_solve(const Spectral& s, double* x, bool add, const Poi
     constexpr bool P = decltype(pr)::value;
     const size_t lds = rows_lds(s.nx);
     if (add)
-      hipLaunchKernelGGL((k_spec_rows_back<E, T, P, true>), dim3(nb), dim3(T), lds, st, x, ps, a);
+      hipLaunchKernelGGL((k_spec_rows_back<E, T, P, true>), dim3(nb, count), dim3(T), lds, st, x, ps, a);
     else
-      hipLaunchKernelGGL((k_spec_rows_back<E, T, P, false>), dim3(nb), dim3(T), lds, st, x, ps, a);
+      hipLaunchKernelGGL((k_spec_rows_back<E, T, P, false>), dim3(nb, count), dim3(T), lds, st, x, ps, a);
   });
 }
 

@@ -318,6 +318,22 @@ __device__ inline void separate_lines(double* D, int n, const Lines& L, int tid,
   __syncthreads();
 }
 
+// Multigrid cycles within which every tolerance that double precision can
+// hold is met (a cycle takes a digit at the least).  A caller who allows fewer
+// may mean the limit to bind, and it counts multigrid cycles: the direct
+// solve, which needs one, is for those who allow this many.
+constexpr int DIRECT_MIN_CYCLES = 20;
+
+// The fields of one of several problems on the same grid, solved by the same
+// launches (blockIdx.y picks the problem).
+struct SpecItem {
+  double* x;
+  const double* f;
+  const PoissonScalars* ps;
+  double* partials;
+  double* hat;
+};
+
 // A direct solver of one periodic grid: plans, tables and the work field.
 struct Spectral {
   bool ok = false;
@@ -336,18 +352,26 @@ struct Spectral {
 
 // Bytes of the work field and the tables (0: the grid has no plan).
 size_t spectral_bytes(int nx, int ny, int nz);
+size_t spectral_table_bytes(int nx, int ny, int nz);   // the tables alone
 // Fills `s` for the grid in `mem` (256-byte aligned) and copies the tables
-// there; s.ok stays false where the grid has no plan or a copy fails.
-void spectral_setup(Spectral& s, char* mem, int nx, int ny, int nz, double h2);
+// there; s.ok stays false where the grid has no plan or a copy fails.  The
+// work field comes first in `mem`; without it (own_field false) `mem` holds
+// the tables alone and the fields come with each launch.
+void spectral_setup(Spectral& s, char* mem, int nx, int ny, int nz, double h2,
+                    bool own_field = true);
 // Right-hand side into the work field, transformed along x and y.  With x
 // (the current iterate) it is the residual f + shift - A x, whose norms (as
 // launch_residual) go to `partials`; the number of blocks is returned.
 // Without x it is f as it is.
+// With `items` the same launches take `count` problems (residual and norms).
 int launch_spectral_forward(const Spectral& s, const double* x, const double* f,
-                            const PoissonScalars* ps, double* partials, hipStream_t st);
+                            const PoissonScalars* ps, double* partials, hipStream_t st,
+                            const SpecItem* items = nullptr, int count = 1);
 int spectral_blocks(const Spectral& s);
 // The rest: along z and back, then x += solution (add) or x = solution.
+// With `items` for `count` problems: x += solution less the mean of the start
+// (psum / n of the problem's scalars), which the solution leaves as it is.
 void launch_spectral_solve(const Spectral& s, double* x, bool add, const PoissonScalars* ps,
-                           hipStream_t st);
+                           hipStream_t st, const SpecItem* items = nullptr, int count = 1);
 
 }  // namespace ek
