@@ -348,8 +348,9 @@ __global__ __launch_bounds__(MAXT) void k_ensemble(RepDev* reps, EnsConst ec) {
 
     // chain (member 0): fields around the beads, then n_sub substeps
     if (R.n_beads > 0 && g == 0) {
-      for (int it = tid; it < R.n_beads * WIN3; it += MAXT)
-        bead_box_item(R.bs, it / WIN3, it % WIN3, fsrc, R.mask, R.psi, lp, d);
+      constexpr int items = WallGeom<1>::ITEMS;
+      for (int it = tid; it < R.n_beads * items; it += MAXT)
+        bead_box_item(R.bs, it / items, it % items, fsrc, R.mask, R.psi, lp, d);
       __syncthreads();
       md_chain<true, TPB, 0, 1, false>(R.bs, R.mp, R.keys, R.vals, R.mask, d, ENS_TABLE_BITS,
                              1 << ec.lds_bits, smem);
@@ -469,7 +470,7 @@ BeadState carve_beads(char* mem, int maxb) {
   s.origin = (int*)take(maxb * 3 * 4 + 4);
   s.mom = (double*)take((size_t)maxb * BOX3 * MOM * 8 + 8);
   s.efield = (double*)take((size_t)maxb * BOX3 * 3 * 8 + 8);
-  s.flags = (unsigned char*)take((size_t)maxb * WIN3 + 8);
+  s.flags = (unsigned long long*)take((size_t)maxb * FLAG_WORDS * 8 + 8);
   s.err = (int*)take(64);
   return s;
 }

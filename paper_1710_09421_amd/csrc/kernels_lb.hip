@@ -90,20 +90,48 @@ __global__ __launch_bounds__(BLOCK) void k_lb_tail(const T* __restrict__ fsrc,
   extern __shared__ int so[];
   const int item = blockIdx.x * blockDim.x + threadIdx.x;
   const int nb_blk = min(n_beads, ((blockIdx.x + 1) * blockDim.x + BOX3 - 1) / BOX3);
-  for (int k = threadIdx.x; k < 3 * nb_blk; k += blockDim.x) so[k] = origin[k];
+  for (int j = threadIdx.x; j < nb_blk; j += blockDim.x) {
+    so[3 * j] = wrap(origin[3 * j], d.nx);
+    so[3 * j + 1] = wrap(origin[3 * j + 1], d.ny);
+    so[3 * j + 2] = wrap(origin[3 * j + 2], d.nz);
+  }
   __syncthreads();
   double acc[7] = {0, 0, 0, 0, 0, 0, 0};
   if (item < n_beads * BOX3) {
+    // a wave per bead: its lanes look for the lower beads whose boxes touch
+    // this one, 64 at a time, and each node is tested against those few only
+    // (against every lower bead the launch took 54 us for 100 beads, mostly
+    // this test)
+    static_assert(BOX3 == 64, "a wave per box");
     const int i = item / BOX3, t = item % BOX3;
-    const int gx = so[3 * i] + t % BOX, gy = so[3 * i + 1] + (t / BOX) % BOX,
-              gz = so[3 * i + 2] + t / (BOX * BOX);
+    const int ox = so[3 * i], oy = so[3 * i + 1], oz = so[3 * i + 2];
+    int x = ox + t % BOX, y = oy + (t / BOX) % BOX, z = oz + t / (BOX * BOX);
+    // v - o reduced to [0, n) for v, o in [0, n + BOX)
+    auto past = [](int v, int o, int n) {
+      const int k = v - o;
+      return k < 0 ? k + n : (k >= n ? k - n : k);
+    };
     bool first = true;
-    for (int j = 0; j < i && first; ++j)
-      if (wrap(gx - so[3 * j], d.nx) < BOX && wrap(gy - so[3 * j + 1], d.ny) < BOX &&
-          wrap(gz - so[3 * j + 2], d.nz) < BOX)
-        first = false;
+    for (int j0 = 0; j0 < i; j0 += 64) {
+      const int j = j0 + t;
+      bool touch = false;
+      if (j < i) {
+        const int ax = past(ox, so[3 * j], d.nx), ay = past(oy, so[3 * j + 1], d.ny),
+                  az = past(oz, so[3 * j + 2], d.nz);
+        touch = (ax < BOX || d.nx - ax < BOX) && (ay < BOX || d.ny - ay < BOX) &&
+                (az < BOX || d.nz - az < BOX);
+      }
+      for (unsigned long long m = __ballot(touch); m; m &= m - 1) {
+        const int k = j0 + __builtin_ctzll(m);
+        if (past(x, so[3 * k], d.nx) < BOX && past(y, so[3 * k + 1], d.ny) < BOX &&
+            past(z, so[3 * k + 2], d.nz) < BOX)
+          first = false;
+      }
+    }
     if (first) {
-      const int x = wrap(gx, d.nx), y = wrap(gy, d.ny), z = wrap(gz, d.nz);
+      x = x >= d.nx ? x - d.nx : x;
+      y = y >= d.ny ? y - d.ny : y;
+      z = z >= d.nz ? z - d.nz : z;
       lb_site<T, I, 7, (V & 1) != 0, (V & 2) != 0>(fsrc, fdst, mask, psi, lp, bt, x, y, z, d,
                                                     acc, 0u, &np, &wv);   // not counted in acc[6]
     }

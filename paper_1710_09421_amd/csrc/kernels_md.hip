@@ -45,7 +45,7 @@ BeadState carve(char* mem, int maxb) {
   s.origin = (int*)take(maxb * 3 * 4 + 4);
   s.mom = (double*)take((size_t)maxb * BOX3 * MOM * 8 + 8);
   s.efield = (double*)take((size_t)maxb * BOX3 * 3 * 8 + 8);
-  s.flags = (unsigned char*)take((size_t)maxb * WIN3_MAX + 8);
+  s.flags = (unsigned long long*)take((size_t)maxb * FLAG_WORDS * 8 + 8);
   s.err = (int*)take(64);
   s.cross = (int*)take((size_t)maxb * 3 * 4 + 4);
   return s;
@@ -83,18 +83,17 @@ __global__ __launch_bounds__(256) void k_bead_box(BeadState bs, const T* __restr
                                                   uint32_t* mask, const double* __restrict__ psi,
                                                   LBParams lp, Dims d, int defer,
                                                   const double* face_q, double inv_eps) {
-  constexpr int items = WallGeom<WR>::W3 > BOX3 ? WallGeom<WR>::W3 : BOX3;
-  for (int t = threadIdx.x; t < items; t += blockDim.x)
+  for (int t = threadIdx.x; t < WallGeom<WR>::ITEMS; t += blockDim.x)
     bead_box_item<T, WR>(bs, blockIdx.x, t, f, mask, psi, lp, d, defer ? mask : nullptr, face_q,
                          inv_eps);
 }
 
-template <bool LDS, int TPB, int NBL, int MAXT, int WR>
+template <bool LDS, int TPB, int NBL, int MAXT, int WR, bool THERMAL>
 __global__ __launch_bounds__(MAXT) void k_md(BeadState bs, MDParams mp, int* gkeys,
                                              long long* gvals, uint32_t* mask, Dims d,
                                              int gbits, int lds_slots) {
   extern __shared__ __align__(16) unsigned char smem[];
-  md_chain<LDS, TPB, NBL, WR>(bs, mp, gkeys, gvals, mask, d, gbits, lds_slots, smem);
+  md_chain<LDS, TPB, NBL, WR, THERMAL>(bs, mp, gkeys, gvals, mask, d, gbits, lds_slots, smem);
 }
 
 // LDS of one workgroup the chain kernel may use: the device's limit for a
@@ -128,7 +127,7 @@ size_t ek::bead_state_bytes(int maxb) {
   size_t t = 0;
   t += align256(maxb * 3 * 8 + 8) * 2 + align256(maxb * 8 + 8) + align256(maxb * 3 * 4 + 4);
   t += align256((size_t)maxb * BOX3 * MOM * 8 + 8) + align256((size_t)maxb * BOX3 * 3 * 8 + 8);
-  t += align256((size_t)maxb * WIN3_MAX + 8) + align256(64);
+  t += align256((size_t)maxb * FLAG_WORDS * 8 + 8) + align256(64);
   t += align256((size_t)maxb * 3 * 4 + 4);   // plane crossing record
   return t;
 }
@@ -246,17 +245,21 @@ ek_status ek_ctx::beads_advance(bool overlap, hipEvent_t chain_end) {
                        HASH_BITS, slots);
     return EK_OK;
   };
-  // the kernel instance for the chain's size and wall reach
-  auto launch = [&](auto wr_tag) -> ek_status {
+  // the kernel instance for the chain's size, wall reach and bead noise (whose
+  // registers the other instances spare)
+  auto launch = [&](auto wr_tag, auto thermal_tag) -> ek_status {
     constexpr int WR = decltype(wr_tag)::value;
-    if (tpb == 8) return md(k_md<true, 8, SMALL_CHAIN / 8, 512, WR>, SMALL_CHAIN / 8);
-    if (tpb == 4) return md(k_md<true, 4, NB_PER_LANE, 512, WR>, NB_PER_LANE);
-    if (tpb == 2) return md(k_md<true, 2, NB_PER_LANE, 512, WR>, NB_PER_LANE);
-    if (threads <= 512) return md(k_md<true, 1, NB_PER_LANE, 512, WR>, NB_PER_LANE);
-    return md(k_md<true, 1, NB_PER_LANE, 1024, WR>, NB_PER_LANE);
+    constexpr bool TH = decltype(thermal_tag)::value;
+    if (tpb == 8) return md(k_md<true, 8, SMALL_CHAIN / 8, 512, WR, TH>, SMALL_CHAIN / 8);
+    if (tpb == 4) return md(k_md<true, 4, NB_PER_LANE, 512, WR, TH>, NB_PER_LANE);
+    if (tpb == 2) return md(k_md<true, 2, NB_PER_LANE, 512, WR, TH>, NB_PER_LANE);
+    if (threads <= 512) return md(k_md<true, 1, NB_PER_LANE, 512, WR, TH>, NB_PER_LANE);
+    return md(k_md<true, 1, NB_PER_LANE, 1024, WR, TH>, NB_PER_LANE);
   };
-  const ek_status lst = wr == 1 ? launch(std::integral_constant<int, 1>{})
-                                : launch(std::integral_constant<int, 2>{});
+  constexpr std::integral_constant<int, 1> wr1{};
+  constexpr std::integral_constant<int, 2> wr2{};
+  const ek_status lst = mp.thermal ? (wr == 1 ? launch(wr1, std::true_type{}) : launch(wr2, std::true_type{}))
+                                   : (wr == 1 ? launch(wr1, std::false_type{}) : launch(wr2, std::false_type{}));
   if (lst) return lst;
   if (chain_end && hipEventRecord(chain_end, cs) != hipSuccess)
     return fail(EK_EHIP, "recording the chain timer failed");

@@ -219,8 +219,8 @@ __global__ __launch_bounds__(64) void k_rep_rearm(const RepDev* __restrict__ rep
 __global__ __launch_bounds__(BLOCK) void k_rep_box(const RepDev* __restrict__ reps, int want, Dims d) {
   const RepDev& R = reps[blockIdx.y];
   if (int(blockIdx.x) >= R.n_beads || !runs(R, want)) return;
-  if (threadIdx.x < WIN3)
-    bead_box_item(R.bs, blockIdx.x, threadIdx.x, (const float*)R.f[R.cur], R.mask, R.psi, R.lp, d);
+  for (int t = threadIdx.x; t < WallGeom<1>::ITEMS; t += BLOCK)
+    bead_box_item(R.bs, blockIdx.x, t, (const float*)R.f[R.cur], R.mask, R.psi, R.lp, d);
 }
 
 // The chains' substeps: a workgroup per replica, eight lanes per bead, pair

@@ -6,6 +6,7 @@
 
 #include <climits>
 #include <cmath>
+#include <type_traits>
 
 #include "ek_internal.h"
 #include "md_table.h"
@@ -15,8 +16,6 @@ namespace ek {
 
 constexpr int BOX = 4;          // moment box edge (nodes floor(R0) - 1 .. floor(R0) + 2)
 constexpr int BOX3 = BOX * BOX * BOX;
-constexpr int WIN = 6;          // flag window edge (nodes floor(R0) - 2 .. floor(R0) + 3)
-constexpr int WIN3 = WIN * WIN * WIN;
 
 // Wall reach WR: the bead-wall WCA looks at the wall sites floor(R) - WR ..
 // floor(R) + 1 + WR in each axis (an S^3 cube around the bead's cell), which
@@ -29,9 +28,11 @@ struct WallGeom {
   static constexpr int S = 2 * WR + 2;
   static constexpr int S3 = S * S * S;
   static constexpr int W = 2 * WR + 4;
-  static constexpr int W3 = W * W * W;
+  static constexpr int ITEMS = 64 * W;   // of bead_box_item: a wave per plane of the window
 };
-constexpr int WIN3_MAX = WallGeom<2>::W3;   // per-bead flag storage of a single context
+// The window's flags, a bit per site: plane wz (8 x 8 bits, site (wx, wy) at
+// wx + 8 wy) of the fluid sites at word wz, of the wall sites at 8 + wz.
+constexpr int FLAG_WORDS = 16;
 constexpr int MOM = 15;         // x[3] (n^a / n), 1/n^a [3], j[3][3]
 
 enum : int { ERR_BOX = 1, ERR_FLUID = 2, ERR_BOND = 4, ERR_TABLE = 8 };
@@ -43,7 +44,7 @@ struct BeadState {
   int* origin;        // [maxb][3] floor(R0) - 1 of the current step
   double* mom;        // [maxb][BOX3][MOM]
   double* efield;     // [maxb][BOX3][3]
-  unsigned char* flags;  // [maxb][W3 of the wall reach]: bit0 fluid, bit1 wall
+  unsigned long long* flags;  // [maxb][FLAG_WORDS] of the window of the wall reach
   int* err;           // error bits
   int* cross = nullptr;  // [maxb][3] plane crossings: first step, last step, net count
 };
@@ -150,6 +151,22 @@ __device__ inline long long round_fixed(double x) {
   return llrint(x);
 }
 
+// Nine values scaled by g and rounded by round_fixed, the test for values
+// beyond its range made once for all of them.
+__device__ inline void round_fixed9(const double (&x)[3][3], double g, long long (&v)[9]) {
+  double y[9], top = 0.0;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) {
+    y[k] = x[k / 3][k % 3] * g;
+    v[k] = __double_as_longlong(y[k] + 6755399441055744.0) - 0x4338000000000000ll;
+    top = fmax(top, fabs(y[k]));
+  }
+  if (__builtin_expect(!(top < 2251799813685248.0), 0)) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) v[k] = round_fixed(y[k]);
+  }
+}
+
 // Node accumulators for the friction impulse: the context's global table, or
 // a table in LDS (sites it has no room for stay in the global table) that is
 // flushed to the global one once after the substeps.  Values are int64 fixed
@@ -161,16 +178,26 @@ struct GlobalNodes {
   int* err;
   int bits;
   __device__ int slot(long long site) { return table_insert(keys, mask, site, err, bits); }
-  __device__ double get(int h, int c) const {
-    return double(ld_i64(&vals[(size_t)h * SLOT_VALUES + 1 + c])) * (1.0 / FIX_FORCE);
+  __device__ void get(int h, long long (&v)[9]) const {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) v[c] = ld_i64(&vals[(size_t)h * SLOT_VALUES + 1 + c]);
   }
-  __device__ void add(int h, int c, long long v) {
-    atomicAdd((unsigned long long*)&vals[(size_t)h * SLOT_VALUES + 1 + c], (unsigned long long)v);
+  __device__ void add(int h, const long long (&v)[9]) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c)
+      atomicAdd((unsigned long long*)&vals[(size_t)h * SLOT_VALUES + 1 + c], (unsigned long long)v[c]);
   }
 };
 
 // LDS probes of an insertion before the site goes to the global table.
 constexpr int LDS_PROBES = 32;
+
+// The nine values of a global slot, 0 without one.
+__device__ inline void gn_get(const GlobalNodes& gn, int h, long long (&v)[9]) {
+#pragma unroll
+  for (int c = 0; c < 9; ++c) v[c] = 0;
+  if (h >= 0) gn.get(h, v);
+}
 
 // The LDS table has any number of slots (positions h = mulhi(mix(site), slots)
 // and linear probing); a site whose probe path holds no free slot within
@@ -196,13 +223,27 @@ struct LdsNodes {
     const int g = global.slot(site);
     return g < 0 ? -1 : -2 - g;
   }
-  __device__ double get(int h, int c) const {
-    if (h >= 0) return double(vals[h * 9 + c]) * (1.0 / FIX_FORCE);
-    return global.get(-2 - h, c);
+  // The nine values of slot code h (0 without a slot).  All LDS reads are
+  // issued before any is used: deciding LDS or global per value took one LDS
+  // round trip and a branch for each of the nine.
+  __device__ void get(int h, long long (&v)[9]) const {
+    const long long* p = vals + (h >= 0 ? h : 0) * 9;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) v[c] = p[c];
+    if (h < 0) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) v[c] = 0;
+      if (h < -1) global.get(-2 - h, v);
+    }
   }
-  __device__ void add(int h, int c, long long v) {
-    if (h >= 0) atomicAdd((unsigned long long*)&vals[h * 9 + c], (unsigned long long)v);
-    else global.add(-2 - h, c, v);
+  __device__ void add(int h, const long long (&v)[9]) {
+    if (h >= 0) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c)
+        atomicAdd((unsigned long long*)&vals[h * 9 + c], (unsigned long long)v[c]);
+    } else {
+      global.add(-2 - h, v);
+    }
   }
 };
 
@@ -216,8 +257,10 @@ struct LdsNodes {
 // (lane l reads lane 7 - l).  A bead's lanes are active together.
 template <int CTRL>
 __device__ inline double dpp_move(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  // every lane has a source, so there is no old value to set up first (which
+  // took as many instructions as the moves)
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
   return __hiloint2double(hi, lo);
 }
 
@@ -283,9 +326,10 @@ __device__ inline void deposit_items(const BeadState& bs, int n, int* keys, long
   }
 }
 
-// Fields of time t around bead i: item t < W3 sets the fluid / wall flags of
-// the flag window (W^3 for the wall reach WR), item t < BOX3 the moments and
-// field of one node of the 4^3 box.  The box origin is written by item 0.
+// Fields of time t around bead i: the 64 items of wave t / 64 (whole waves
+// call it) set one plane of the fluid / wall flags of the flag window (W
+// planes for the wall reach WR), item t < BOX3 the moments and field of one
+// node of the 4^3 box.  The box origin is written by item 0.
 // With `defer` set, every box node is also flagged MASK_DEFER: the chain's
 // friction can only reach nodes of the boxes, so the lattice update of all
 // other sites need not wait for it.
@@ -306,15 +350,29 @@ __device__ inline void bead_box_item(const BeadState& bs, int i, int t, const T*
     bs.origin[3 * i + 2] = bz;
   }
   using G = WallGeom<WR>;
-  if (t < G::W3) {
-    const int wx = t % G::W, wy = (t / G::W) % G::W, wz = t / (G::W * G::W);
-    const uint32_t m = mask[site_of(bx - WR + wx, by - WR + wy, bz - WR + wz, d)];
-    bs.flags[(size_t)i * G::W3 + t] =
-        (unsigned char)(((m & MASK_SOLID) ? 0 : 1) | ((m & MASK_WALL) ? 2 : 0));
+  if (t < G::ITEMS) {
+    const int wx = t & 7, wy = (t >> 3) & 7, wz = t >> 6;
+    const bool in = wx < G::W && wy < G::W;
+    uint32_t m = MASK_SOLID;
+    if (in) m = mask[site_of(bx - WR + wx, by - WR + wy, bz - WR + wz, d)];
+    const unsigned long long fluid = __ballot(in && !(m & MASK_SOLID));
+    const unsigned long long wall = __ballot(in && (m & MASK_WALL));
+    if ((t & 63) == 0) {
+      bs.flags[(size_t)i * FLAG_WORDS + wz] = fluid;
+      bs.flags[(size_t)i * FLAG_WORDS + 8 + wz] = wall;
+    }
   }
   if (t >= BOX3) return;
   const int cx = bx + t % BOX, cy = by + (t / BOX) % BOX, cz = bz + t / (BOX * BOX);
-  const long long r = site_of(cx, cy, cz, d);
+  // offsets of the node and its neighbours along each axis: three divisions
+  // (the wraps) in all, where one per pulled site cost more than the pulls
+  const int x = wrap(cx, d.nx), y = wrap(cy, d.ny), z = wrap(cz, d.nz);
+  const long long nxy = (long long)d.nx * d.ny;
+  const long long xo[3] = {x == 0 ? d.nx - 1 : x - 1, x, x == d.nx - 1 ? 0 : x + 1};
+  const long long yo[3] = {(y == 0 ? d.ny - 1 : y - 1) * (long long)d.nx, y * (long long)d.nx,
+                           (y == d.ny - 1 ? 0 : y + 1) * (long long)d.nx};
+  const long long zo[3] = {(z == 0 ? d.nz - 1 : z - 1) * nxy, z * nxy, (z == d.nz - 1 ? 0 : z + 1) * nxy};
+  const long long r = zo[1] + yo[1] + xo[1];
   if (defer) atomicOr(&defer[r], MASK_DEFER);
   const uint32_t m = mask[r];
   double* mo = bs.mom + ((size_t)i * BOX3 + t) * MOM;
@@ -323,12 +381,11 @@ __device__ inline void bead_box_item(const BeadState& bs, int i, int t, const T*
 #pragma unroll
   for (int c = 0; c < MOM; ++c) v[c] = 0.0;
   if (!(m & MASK_SOLID)) {
-    const int x = wrap(cx, d.nx), y = wrap(cy, d.ny), z = wrap(cz, d.nz);
     T g[3][Q];
 #pragma unroll
     for (int p = 0; p < Q; ++p) {
       const bool bounce = (m >> p) & 1u;
-      const long long src = bounce ? r : site_of(x - CX[p], y - CY[p], z - CZ[p], d);
+      const long long src = bounce ? r : zo[1 - CZ[p]] + yo[1 - CY[p]] + xo[1 - CX[p]];
       const int q = bounce ? OPP[p] : p;
 #pragma unroll
       for (int s = 0; s < 3; ++s) g[s][p] = f[(size_t)(s * Q + q) * d.n + src];
@@ -371,14 +428,14 @@ __device__ inline void bead_box_item(const BeadState& bs, int i, int t, const T*
     auto side = [&](int bit, long long idx) {
       return ((m >> bit) & 1u) ? pc + face_q[idx] * inv_eps : psi[idx];
     };
-    e[0] = -0.5 * (side(2, site_of(cx + 1, cy, cz, d)) - side(1, site_of(cx - 1, cy, cz, d))) + lp.eext[0];
-    e[1] = -0.5 * (side(4, site_of(cx, cy + 1, cz, d)) - side(3, site_of(cx, cy - 1, cz, d))) + lp.eext[1];
-    e[2] = -0.5 * (side(6, site_of(cx, cy, cz + 1, d)) - side(5, site_of(cx, cy, cz - 1, d))) + lp.eext[2];
+    e[0] = -0.5 * (side(2, r - xo[1] + xo[2]) - side(1, r - xo[1] + xo[0])) + lp.eext[0];
+    e[1] = -0.5 * (side(4, r - yo[1] + yo[2]) - side(3, r - yo[1] + yo[0])) + lp.eext[1];
+    e[2] = -0.5 * (side(6, r - zo[1] + zo[2]) - side(5, r - zo[1] + zo[0])) + lp.eext[2];
     return;
   }
-  e[0] = -0.5 * (psi[site_of(cx + 1, cy, cz, d)] - psi[site_of(cx - 1, cy, cz, d)]) + lp.eext[0];
-  e[1] = -0.5 * (psi[site_of(cx, cy + 1, cz, d)] - psi[site_of(cx, cy - 1, cz, d)]) + lp.eext[1];
-  e[2] = -0.5 * (psi[site_of(cx, cy, cz + 1, d)] - psi[site_of(cx, cy, cz - 1, d)]) + lp.eext[2];
+  e[0] = -0.5 * (psi[r - xo[1] + xo[2]] - psi[r - xo[1] + xo[0]]) + lp.eext[0];
+  e[1] = -0.5 * (psi[r - yo[1] + yo[2]] - psi[r - yo[1] + yo[0]]) + lp.eext[1];
+  e[2] = -0.5 * (psi[r - zo[1] + zo[2]] - psi[r - zo[1] + zo[0]]) + lp.eext[2];
 }
 
 // Pair partners kept per lane: lane l of bead i lists the beads j = l,
@@ -399,6 +456,16 @@ __host__ __device__ inline size_t md_list_bytes(int threads, int nbl) {
   return (size_t)threads * nbl * sizeof(unsigned short);
 }
 
+// What bounds it: one workgroup on one compute unit, so a chain of 8 beads (a
+// single wave) is a serial chain of some 500 vector instructions and three
+// LDS round trips a substep, and one of 64 beads (two waves a SIMD) is bound
+// by issue.  Hence no branch or wait per value where nine values are read or
+// added together, lane moves without a value to replace, divisions off the
+// chain, and reads issued before what they are needed for.  Measured for 8,
+// 32, 64 and 100 beads: 1.75, 2.4, 3.2 and 4.2 us a substep (2.9, 3.1, 3.9 and
+// 5.2 before), and 9 to 30 us for what comes before and after them (one
+// substep of 100 beads with WR = 2: 48 us instead of 99).
+//
 // n_sub substeps of one chain by one workgroup (TPB lanes per bead; the
 // threads beyond n * TPB only take part in the barriers).  smem: LDS for the
 // bead positions, when LDS is set the node table of lds_slots slots (sites
@@ -412,7 +479,6 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
                                 long long* gvals, uint32_t* mask, const Dims& d, int gbits,
                                 int lds_slots, unsigned char* smem) {
   using G = WallGeom<WR>;
-  constexpr int WIN = G::W;                                    // flag window edge
   constexpr int CPL = 8 / TPB;                                 // corners per lane
   double* sR = (double*)smem;                                  // [3 * n]
   long long* lvals = (long long*)(smem + (((size_t)mp.n * 24 + 15) & ~size_t(15)));
@@ -422,10 +488,12 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
   // LDS node table
   constexpr bool NLIST = NBL > 0;
   unsigned short* nbl = (unsigned short*)(lkeys + lslots);
-  __shared__ int s_rebuild, s_overflow;
+  __shared__ int s_rebuild, s_overflow, s_image;
   if (NLIST && threadIdx.x == 0) {
-    s_rebuild = 1;
-    s_overflow = 0;
+    // a single substep walks all pairs once, as the list's build would
+    s_rebuild = mp.n_sub > 1;
+    s_overflow = mp.n_sub > 1 ? 0 : 1;
+    s_image = 0;
   }
   int nb_count = 0;
   double Rb[3] = {0, 0, 0};                 // position at the last list build
@@ -434,10 +502,8 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
   const int lane = threadIdx.x % TPB;
   const bool live = i < mp.n;
   if (LDS) {
-    for (int h = threadIdx.x; h < lslots; h += blockDim.x) {
-      lkeys[h] = -1;
-      for (int c = 0; c < 9; ++c) lvals[(size_t)h * 9 + c] = 0;
-    }
+    for (int h = threadIdx.x; h < lslots; h += blockDim.x) lkeys[h] = -1;
+    for (int h = threadIdx.x; h < lslots * 9; h += blockDim.x) lvals[h] = 0;
   }
   double R[3] = {0, 0, 0}, V[3] = {0, 0, 0}, q = 0.0;
   int org[3] = {0, 0, 0};
@@ -465,22 +531,22 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
   const double iR02 = 1.0 / (mp.R0 * mp.R0);
   const double* mom = bs.mom + (size_t)(live ? i : 0) * BOX3 * MOM;
   const double* ef = bs.efield + (size_t)(live ? i : 0) * BOX3 * 3;
-  const unsigned char* fl = bs.flags + (size_t)(live ? i : 0) * G::W3;
-  int cell[3] = {INT_MIN, INT_MIN, INT_MIN};
+  const unsigned long long* fl = bs.flags + (size_t)(live ? i : 0) * FLAG_WORDS;
+  int cell[3] = {0, 0, 0};
   int slot[CPL], bidx[CPL];
   double wfl[CPL];
-  double fl_all[8];                 // fluid flag of every corner (for the normalisation)
-  // With at most two corners per lane the corner data, which is fixed for the
-  // whole step (node momenta of time t and the field), and the lane's
-  // wall-site flags are kept in registers from the substep the bead enters
-  // its cell on; with more corners per lane they are read each substep.
+  // With at most two corners per lane the node momenta of time t, which are
+  // fixed for the whole step, and (up to four corners) the lane's wall-site
+  // flags are kept in registers from the substep the bead enters its cell on;
+  // with more corners per lane they are read each substep.
   constexpr bool CACHE = CPL <= 2;   // node momenta too
-  constexpr bool CACHE_E = CPL <= 4; // field and wall flags
-  constexpr int NWS = G::S3 / TPB;  // wall sites per lane
-  static_assert(G::S3 % TPB == 0, "wall sites split evenly over a bead's lanes");
-  constexpr int NWB = (NWS + 63) / 64;
+  constexpr bool CACHE_W = CPL <= 4; // wall flags
+  // wall sites around the cell: the lanes share the S^2 columns of the cube;
+  // a word of wall_bits holds the S sites of each of CPW columns
+  constexpr int COLS = (G::S * G::S + TPB - 1) / TPB;   // columns per lane
+  constexpr int CPW = 64 / G::S;
+  constexpr int NWB = (COLS + CPW - 1) / CPW;
   double mo_c[CACHE ? CPL : 1][MOM];
-  double e_c[CACHE_E ? CPL : 1][3];
   unsigned long long wall_bits[NWB];
 #pragma unroll
   for (int b = 0; b < NWB; ++b) wall_bits[b] = 0;
@@ -489,27 +555,144 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
   // this step's solve (the electrostatic forces on ions, walls and beads then
   // cancel exactly, and the bead never feels its own deposited charge)
   double qe[3] = {0.0, 0.0, 0.0};
+  if (live) {   // the bead starts in the middle cell of its box
+    const double dx = R[0] - floor(R[0]), dy = R[1] - floor(R[1]), dz = R[2] - floor(R[2]);
+    double w[CPL], wsum = 0.0;
+#pragma unroll
+    for (int a = 0; a < CPL; ++a) {
+      const int k8 = lane * CPL + a;
+      const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
+      w[a] = (ox ? dx : 1.0 - dx) * (oy ? dy : 1.0 - dy) * (oz ? dz : 1.0 - dz);
+      if (mp.field_fluid) {
+        w[a] *= (fl[1 + WR + oz] >> ((1 + WR + ox) + 8 * (1 + WR + oy))) & 1 ? 1.0 : 0.0;
+        wsum += w[a];
+      }
+    }
+    if (mp.field_fluid) {
+      wsum = group_sum<TPB>(wsum);
+#pragma unroll
+      for (int a = 0; a < CPL; ++a) w[a] /= wsum > 0.0 ? wsum : 1.0;
+    }
+#pragma unroll
+    for (int a = 0; a < CPL; ++a) {
+      const int k8 = lane * CPL + a;
+      const double* e =
+          ef + 3 * ((1 + (k8 & 1)) + BOX * ((1 + ((k8 >> 1) & 1)) + BOX * (1 + ((k8 >> 2) & 1))));
+#pragma unroll
+      for (int c = 0; c < 3; ++c) qe[c] += q * w[a] * e[c];
+    }
+  }
+  const int wall_lim = int(ceil(rc2));   // integer distances^2 below rc2 are below this
+  // The bead in the cell at (fx, fy, fz), corner 0 at (lx, ly, lz) of its box:
+  // the corners' slots and node momenta, and of the wall sites (site
+  // floor(R) - WR + w at window index (lx + w)) those closer than the cut-off
+  // to some point of the cell.  The reads do not depend on each other and so
+  // overlap (a byte per site behind a test each had taken a round trip to
+  // memory for every site: 99 us for one substep of 100 beads with WR = 2).
+  auto enter = [&](int fx, int fy, int fz, int lx, int ly, int lz) {
+#pragma unroll
+    for (int a = 0; a < CPL; ++a) {
+      const int k8 = lane * CPL + a;
+      const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
+      bidx[a] = (lx + ox) + BOX * ((ly + oy) + BOX * (lz + oz));
+      wfl[a] = (fl[lz + oz + WR] >> ((lx + ox + WR) + 8 * (ly + oy + WR))) & 1 ? 1.0 : 0.0;
+      if constexpr (CACHE) {
+        const double* mo = mom + (size_t)bidx[a] * MOM;
+#pragma unroll
+        for (int c = 0; c < MOM; ++c) mo_c[CACHE ? a : 0][c] = mo[c];   // 0 at solid nodes
+      }
+    }
+    if constexpr (CACHE_W) {
+      unsigned long long plane[G::S];
+#pragma unroll
+      for (int k = 0; k < G::S; ++k) plane[k] = fl[8 + lz + k];
+#pragma unroll
+      for (int b = 0; b < NWB; ++b) wall_bits[b] = 0;
+#pragma unroll 1
+      for (int u = 0; u < COLS; ++u) {
+        const int p = lane + u * TPB, wx = p % G::S, wy = p / G::S;
+        const int gx = max(WR - wx, wx - WR - 1), gy = max(WR - wy, wy - WR - 1);   // to the cell's edge
+        const int shift = ((lx + wx) + 8 * (ly + wy)) & 63, near = gx * gx + gy * gy - wall_lim;
+        unsigned column = 0;
+#pragma unroll
+        for (int k = 0; k < G::S; ++k) {
+          const int gz = k < WR ? WR - k : (k > WR + 1 ? k - WR - 1 : 0);
+          // the flag, if near + gz^2 is negative
+          column |= (unsigned(plane[k] >> shift) & (unsigned(near + gz * gz) >> 31)) << k;
+        }
+        if (p >= G::S * G::S) column = 0;
+#pragma unroll
+        for (int b = 0; b < NWB; ++b) {
+          const int at = u - b * CPW;
+          if (at >= 0 && at < CPW) wall_bits[b] |= (unsigned long long)column << (at * G::S);
+        }
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < CPL; ++a) {
+      const int k8 = lane * CPL + a;
+      const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
+      slot[a] = -1;
+      if (wfl[a] != 0.0) {
+        const long long site = site_of(fx + ox, fy + oy, fz + oz, d);
+        slot[a] = LDS ? ln.slot(site) : gn.slot(site);
+      }
+    }
+  };
+  if (live) {   // the start: the middle cell of the box
+#pragma unroll
+    for (int c = 0; c < 3; ++c) cell[c] = int(floor(R[c]));
+    enter(cell[0], cell[1], cell[2], 1, 1, 1);
+  }
   const double rl = 1.122462048309373 * mp.sigma + NB_SKIN;      // list radius
   const double rl2 = rl * rl, half_skin2 = 0.25 * NB_SKIN * NB_SKIN;
+  // the lane's first partners (the bead itself past the end): their positions
+  // are read at the substep's start, without a look at the list (eight lanes a
+  // bead: with fewer the registers are not spared)
+  constexpr int CH = 4;
+  constexpr bool HEAD = NLIST && TPB == 8;
+  int head[CH];
+#pragma unroll
+  for (int u = 0; u < CH; ++u) head[u] = live ? i : 0;
   for (int sub = 0; sub < mp.n_sub; ++sub) {
     if (NLIST && s_rebuild) {            // the same in every thread (set before the last barrier)
       if (live) {
         nb_count = 0;
-        for (int j = lane; j < mp.n; j += TPB) {
-          if (j == i || (mp.bond == 1 && (j == i - 1 || j == i + 1))) continue;
-          double r2 = 0.0;
+        constexpr int AHEAD = 4;   // candidates whose positions are read together
+        for (int j0 = lane; j0 < mp.n; j0 += AHEAD * TPB) {
+          double P[AHEAD][3];
 #pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const double v = R[c] - sR[3 * j + c];
-            const double dv = v - L[c] * rint(v * iL[c]);
-            r2 += dv * dv;
+          for (int u = 0; u < AHEAD; ++u) {
+            const int j = j0 + u * TPB < mp.n ? j0 + u * TPB : i;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) P[u][c] = sR[3 * j + c];
           }
-          if (r2 < rl2) {
-            if (nb_count < NBL) nbl[nb_count * blockDim.x + threadIdx.x] = (unsigned short)j;
-            ++nb_count;
+#pragma unroll
+          for (int u = 0; u < AHEAD; ++u) {
+            const int j = j0 + u * TPB;
+            if (j >= mp.n || j == i) continue;
+            double r2 = 0.0;
+            bool image = false;   // of the pair, now or before the next build
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+              const double v = R[c] - P[u][c];
+              const double dv = v - L[c] * rint(v * iL[c]);
+              r2 += dv * dv;
+              image = image || !(fabs(v) + NB_SKIN < 0.5 * L[c]);
+            }
+            const bool bonded = j == i - 1 || j == i + 1;
+            if (image && (bonded || r2 < rl2)) s_image = 1;
+            if (mp.bond == 1 && bonded) continue;
+            if (r2 < rl2) {
+              if (nb_count < NBL) nbl[nb_count * blockDim.x + threadIdx.x] = (unsigned short)j;
+              ++nb_count;
+            }
           }
         }
         if (nb_count > NBL) s_overflow = 1;
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+          head[u] = HEAD && u < nb_count ? int(nbl[u * blockDim.x + threadIdx.x]) : i;
 #pragma unroll
         for (int c = 0; c < 3; ++c) Rb[c] = R[c];
       }
@@ -534,68 +717,30 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
           ly = min(max(ly, 0), BOX - 2);
           lz = min(max(lz, 0), BOX - 2);
         }
-#pragma unroll
-        for (int k8 = 0; k8 < 8; ++k8) {
-          const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
-          const int wi = (lx + ox + WR) + WIN * ((ly + oy + WR) + WIN * (lz + oz + WR));
-          fl_all[k8] = (fl[wi] & 1) ? 1.0 : 0.0;
-        }
-#pragma unroll
-        for (int a = 0; a < CPL; ++a) {
-          const int k8 = lane * CPL + a;
-          const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
-          bidx[a] = (lx + ox) + BOX * ((ly + oy) + BOX * (lz + oz));
-          // from the flag window, not fl_all[k8]: k8 depends on the lane, and
-          // a register array indexed at run time would live in scratch memory
-          wfl[a] = (fl[(lx + ox + WR) + WIN * ((ly + oy + WR) + WIN * (lz + oz + WR))] & 1) ? 1.0 : 0.0;
-          slot[a] = -1;
-          if (wfl[a] != 0.0) {
-            const long long site = site_of(fx + ox, fy + oy, fz + oz, d);
-            slot[a] = LDS ? ln.slot(site) : gn.slot(site);
-          }
-          if constexpr (CACHE_E) {
-            const double* e = ef + (size_t)bidx[a] * 3;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) e_c[CACHE_E ? a : 0][c] = e[c];
-          }
-          if constexpr (CACHE) {
-            const double* mo = mom + (size_t)bidx[a] * MOM;
-#pragma unroll
-            for (int c = 0; c < MOM; ++c) {   // read unconditionally: not behind the flag's read
-              const double m = mo[c];
-              mo_c[CACHE ? a : 0][c] = wfl[a] != 0.0 ? m : 0.0;
-            }
-          }
-        }
-        if constexpr (CACHE_E) {
-#pragma unroll
-          for (int b = 0; b < NWB; ++b) wall_bits[b] = 0;
-#pragma unroll
-          for (int k = 0; k < NWS; ++k) {
-            const int wsite = lane + k * TPB;
-            const int wx = wsite % G::S, wy = (wsite / G::S) % G::S, wz = wsite / (G::S * G::S);
-            // site floor(R) - WR + w sits at window index (floor(R) - org) + w
-            const int ix = lx + wx, iy = ly + wy, iz = lz + wz;
-            if (ix < 0 || ix >= WIN || iy < 0 || iy >= WIN || iz < 0 || iz >= WIN) continue;
-            if (fl[ix + WIN * (iy + WIN * iz)] & 2) wall_bits[k >> 6] |= 1ull << (k & 63);
-          }
-        }
+        enter(fx, fy, fz, lx, ly, lz);
       }
       // impulse of earlier substeps on this lane's corners, read before the
       // weights so that the reads overlap their arithmetic (one corner per
       // lane: with more the registers are not spared)
       constexpr bool PRE_K = CPL == 1;
-      double kpre[PRE_K ? CPL : 1][9];
+      long long kpre[9];
       if constexpr (PRE_K) {
-#pragma unroll
-        for (int a = 0; a < CPL; ++a)
-#pragma unroll
-          for (int k = 0; k < 9; ++k)
-            kpre[a][k] = slot[a] == -1 ? 0.0 : (LDS ? ln.get(slot[a], k) : gn.get(slot[a], k));
+        if constexpr (LDS) ln.get(slot[0], kpre);
+        else gn_get(gn, slot[0], kpre);
       }
-      // plain and fluid-renormalised trilinear weights; with the occupation
-      // cube, its node indicator per axis (offset 0: d < sigma/2, offset 1:
-      // d >= 1 - sigma/2) renormalised over the fluid nodes
+      // and the first partners' positions
+      double P0[HEAD ? CH : 1][3];
+      if constexpr (HEAD) {
+#pragma unroll
+        for (int u = 0; u < CH; ++u)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) P0[HEAD ? u : 0][c] = sR[3 * head[u] + c];
+      }
+      // The corners' plain trilinear weights over the fluid, or, with the
+      // occupation cube, its node indicator per axis (offset 0: d < sigma/2,
+      // offset 1: d >= 1 - sigma/2); both are renormalised over the fluid
+      // corners.  The sums below take the weights as they are and are divided
+      // by their sum afterwards, so the division does not stand before them.
       auto cube = [&](int ox, int oy, int oz) {
         const double hs = mp.half_sigma;
         return ((ox ? dx >= 1.0 - hs : dx < hs) && (oy ? dy >= 1.0 - hs : dy < hs) &&
@@ -603,52 +748,52 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
       };
       double wsum = 0.0, wsum_c = 0.0;
 #pragma unroll
-      for (int k8 = 0; k8 < 8; ++k8) {
+      for (int a = 0; a < CPL; ++a) {
+        const int k8 = lane * CPL + a;
         const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
-        wsum += fl_all[k8] * (ox ? dx : 1.0 - dx) * (oy ? dy : 1.0 - dy) * (oz ? dz : 1.0 - dz);
-        if (mp.theta) wsum_c += fl_all[k8] * cube(ox, oy, oz);
+        wt[a] = (ox ? dx : 1.0 - dx) * (oy ? dy : 1.0 - dy) * (oz ? dz : 1.0 - dz) * wfl[a];
+        wsum += wt[a];
+        if (mp.theta) {
+          wt[a] = cube(ox, oy, oz) * wfl[a];
+          wsum_c += wt[a];
+        }
       }
-      if (!mp.theta) wsum_c = wsum;
+      wsum = group_sum<TPB>(wsum);
+      wsum_c = mp.theta ? group_sum<TPB>(wsum_c) : wsum;
       if (!(wsum_c > 0.0) || !(wsum > 0.0)) {
         if (lane == 0) atomicOr(bs.err, ERR_FLUID);
-        wsum = wsum > 0.0 ? wsum : 1.0;
         wsum_c = wsum_c > 0.0 ? wsum_c : 1.0;
       }
       const double iws = 1.0 / wsum_c;
       // this lane's corners: velocities from the node momentum (populations of
-      // time t plus the friction impulse of earlier substeps), composition,
-      // and on the first substep the electric field with the plain weights
+      // time t plus the friction impulse of earlier substeps) and composition
       double acc[12];
 #pragma unroll
       for (int c = 0; c < 12; ++c) acc[c] = 0.0;
 #pragma unroll
       for (int a = 0; a < CPL; ++a) {
-        const int k8 = lane * CPL + a;
-        const int ox = k8 & 1, oy = (k8 >> 1) & 1, oz = (k8 >> 2) & 1;
-        const double w = (ox ? dx : 1.0 - dx) * (oy ? dy : 1.0 - dy) * (oz ? dz : 1.0 - dz);
-        wt[a] = (mp.theta ? cube(ox, oy, oz) : w) * wfl[a] * iws;
-        if (sub == 0) {
-          const double* e = CACHE_E ? e_c[CACHE_E ? a : 0] : ef + (size_t)bidx[a] * 3;
-          const double we = mp.field_fluid ? w * wfl[a] / wsum : w;
-#pragma unroll
-          for (int c = 0; c < 3; ++c) qe[c] += q * we * e[c];
-        }
         if (wt[a] != 0.0) {
           const double* mo = CACHE ? mo_c[CACHE ? a : 0] : mom + (size_t)bidx[a] * MOM;
+          long long kv[9];
+          if constexpr (PRE_K) {
+#pragma unroll
+            for (int k = 0; k < 9; ++k) kv[k] = kpre[k];
+          } else {
+            if constexpr (LDS) ln.get(slot[a], kv);
+            else gn_get(gn, slot[a], kv);
+          }
 #pragma unroll
           for (int s = 0; s < 3; ++s) {
             acc[9 + s] += wt[a] * mo[s];
+            const double wn = wt[a] * mo[3 + s];
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-              const double kacc =
-                  PRE_K ? kpre[PRE_K ? a : 0][3 * s + c]
-                        : (slot[a] == -1 ? 0.0 : (LDS ? ln.get(slot[a], 3 * s + c)
-                                                    : gn.get(slot[a], 3 * s + c)));
-              acc[3 * s + c] += wt[a] * (mo[6 + 3 * s + c] + kacc) * mo[3 + s];
-            }
+            for (int c = 0; c < 3; ++c)
+              acc[3 * s + c] += wn * (mo[6 + 3 * s + c] + double(kv[3 * s + c]) * (1.0 / FIX_FORCE));
           }
         }
       }
+#pragma unroll
+      for (int a = 0; a < CPL; ++a) wt[a] *= iws;
       // this lane's share of the conservative forces
       double F[3] = {0.0, 0.0, 0.0};
       // FENE bonds: the bond to i - 1 on lane 0 and the one to i + 1 on lane
@@ -668,12 +813,13 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
           for (int c = 0; c < 3; ++c) PB[PRE_B ? k : 0][c] = sR[3 * j + c];
         }
       }
-      auto wca_at = [&](const double* P) {   // WCA with a partner at P
+      // IMAGE: nearest images (without it no pair of the list or bond has one)
+      auto wca_at = [&](const double* P, auto IMAGE) {   // WCA with a partner at P
         double dv[3], r2 = 0.0;
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
           const double v = R[c] - P[c];
-          dv[c] = v - L[c] * rint(v * iL[c]);
+          dv[c] = IMAGE ? v - L[c] * rint(v * iL[c]) : v;
           r2 += dv[c] * dv[c];
         }
         if (r2 < rc2) {
@@ -684,32 +830,54 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
           for (int c = 0; c < 3; ++c) F[c] += coef * dv[c];
         }
       };
+      constexpr std::true_type images{};
+      constexpr std::false_type no_images{};
+      const bool image = !NLIST || __builtin_amdgcn_readfirstlane(s_image | s_overflow) != 0;
       if (NLIST && !s_overflow) {                    // WCA with the listed partners
         // four partners at a time: their indices, then their positions, are
         // read together (one LDS round trip each), the terms are added in
         // list order
-        constexpr int CH = 4;
         static_assert(NBL % CH == 0, "list chunks");
-        for (int k0 = 0; k0 < nb_count; k0 += CH) {
-          int jj[CH];
+        auto listed = [&](auto IMAGE) {
+          if constexpr (HEAD) {
 #pragma unroll
-          for (int u = 0; u < CH; ++u)
-            jj[u] = k0 + u < nb_count ? int(nbl[(k0 + u) * blockDim.x + threadIdx.x]) : i;
-          double P[CH][3];
-#pragma unroll
-          for (int u = 0; u < CH; ++u)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) P[u][c] = sR[3 * jj[u] + c];
-#pragma unroll
-          for (int u = 0; u < CH; ++u)
-            if (k0 + u < nb_count) wca_at(P[u]);
-        }
-      } else {
-        for (int j = lane; j < mp.n; j += TPB)       // WCA between all pairs
-          if (j != i && !(mp.bond == 1 && (j == i - 1 || j == i + 1))) {
-            const double P[3] = {sR[3 * j], sR[3 * j + 1], sR[3 * j + 2]};
-            wca_at(P);
+            for (int u = 0; u < CH; ++u)
+              if (u < nb_count) wca_at(P0[HEAD ? u : 0], IMAGE);
           }
+          for (int k0 = HEAD ? CH : 0; k0 < nb_count; k0 += CH) {
+            int jj[CH];
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+              jj[u] = k0 + u < nb_count ? int(nbl[(k0 + u) * blockDim.x + threadIdx.x]) : i;
+            double P[CH][3];
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+#pragma unroll
+              for (int c = 0; c < 3; ++c) P[u][c] = sR[3 * jj[u] + c];
+#pragma unroll
+            for (int u = 0; u < CH; ++u)
+              if (k0 + u < nb_count) wca_at(P[u], IMAGE);
+          }
+        };
+        if (image) listed(images);
+        else listed(no_images);
+      } else {
+        constexpr int AHEAD = NLIST ? 4 : 1;         // WCA between all pairs
+        for (int j0 = lane; j0 < mp.n; j0 += AHEAD * TPB) {
+          double P[AHEAD][3];
+#pragma unroll
+          for (int u = 0; u < AHEAD; ++u) {
+            const int j = j0 + u * TPB < mp.n ? j0 + u * TPB : i;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) P[u][c] = sR[3 * j + c];
+          }
+#pragma unroll
+          for (int u = 0; u < AHEAD; ++u) {
+            const int j = j0 + u * TPB;
+            if (j < mp.n && j != i && !(mp.bond == 1 && (j == i - 1 || j == i + 1)))
+              wca_at(P[u], images);
+          }
+        }
       }
       // WCA against wall-site centres: site k of this lane is lane + k TPB of
       // the S^3 sites around the bead's cell
@@ -724,23 +892,26 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
           for (int c = 0; c < 3; ++c) F[c] += coef * dv[c];
         }
       };
-      if constexpr (CACHE_E) {
+      if constexpr (CACHE_W) {
         // only the wall sites among them, in increasing k
 #pragma unroll
         for (int b = 0; b < NWB; ++b)
           for (unsigned long long mb = wall_bits[b]; mb; mb &= mb - 1) {
-            const int wsite = lane + (64 * b + __builtin_ctzll(mb)) * TPB;
-            wall_at(fx - WR + wsite % G::S, fy - WR + (wsite / G::S) % G::S,
-                    fz - WR + wsite / (G::S * G::S));
+            const int k = __builtin_ctzll(mb), u = k / G::S;
+            const int wz = k - u * G::S, p = lane + (b * CPW + u) * TPB;
+            wall_at(fx - WR + p % G::S, fy - WR + p / G::S, fz - WR + wz);
           }
       } else {
-        for (int k = 0; k < NWS; ++k) {
-          const int wsite = lane + k * TPB;
-          const int wx = wsite % G::S, wy = (wsite / G::S) % G::S, wz = wsite / (G::S * G::S);
-          const int ix = lx + wx, iy = ly + wy, iz = lz + wz;
-          if (ix < 0 || ix >= WIN || iy < 0 || iy >= WIN || iz < 0 || iz >= WIN) continue;
-          if (!(fl[ix + WIN * (iy + WIN * iz)] & 2)) continue;
-          wall_at(fx - WR + wx, fy - WR + wy, fz - WR + wz);
+        // lx, ly, lz as at the last entry of a cell
+        const int bx = bidx[0] % BOX, by = (bidx[0] / BOX) % BOX, bz = bidx[0] / (BOX * BOX);
+        const int cx = bx - (lane * CPL & 1), cy = by - ((lane * CPL >> 1) & 1), cz = bz - ((lane * CPL >> 2) & 1);
+        for (int wz = 0; wz < G::S; ++wz) {
+          const unsigned long long plane = fl[8 + cz + wz];
+          if (plane == 0) continue;
+          for (int p = lane; p < G::S * G::S; p += TPB) {
+            const int wx = p % G::S, wy = p / G::S;
+            if ((plane >> ((cx + wx) + 8 * (cy + wy))) & 1) wall_at(fx - WR + wx, fy - WR + wy, fz - WR + wz);
+          }
         }
       }
       if (bond_lane) {
@@ -752,7 +923,7 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
             const double v = (PRE_B ? PB[PRE_B ? k : 0][c] : sR[3 * j + c]) - R[c];
-            dv[c] = v - L[c] * rint(v * iL[c]);
+            dv[c] = image ? v - L[c] * rint(v * iL[c]) : v;
             r2 += dv[c] * dv[c];
           }
           double coef;
@@ -776,7 +947,7 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
 #pragma unroll
       for (int c = 0; c < 3; ++c) F[c] += qe[c];
 #pragma unroll
-      for (int c = 0; c < 12; ++c) acc[c] = group_sum<TPB>(acc[c]);
+      for (int c = 0; c < 12; ++c) acc[c] = group_sum<TPB>(acc[c]) * iws;
 #pragma unroll
       for (int c = 0; c < 3; ++c) F[c] = group_sum<TPB>(F[c]);
       // friction of each species (with the thermal noise shared by the
@@ -808,15 +979,10 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
 #pragma unroll
       for (int a = 0; a < CPL; ++a) {
         if (wt[a] == 0.0 || slot[a] == -1) continue;
-        const double g = -h * wt[a] * FIX_FORCE;   // impulse scale of this corner
-#pragma unroll
-        for (int s = 0; s < 3; ++s)
-#pragma unroll
-          for (int c = 0; c < 3; ++c) {
-            const long long v = round_fixed(phi[s][c] * g);
-            if (LDS) ln.add(slot[a], 3 * s + c, v);
-            else gn.add(slot[a], 3 * s + c, v);
-          }
+        long long v[9];
+        round_fixed9(phi, -h * wt[a] * FIX_FORCE, v);   // scaled to this corner's impulse
+        if constexpr (LDS) ln.add(slot[a], v);
+        else gn.add(slot[a], v);
       }
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
@@ -854,14 +1020,30 @@ __device__ inline void md_chain(const BeadState& bs, const MDParams& mp, int* gk
   }
   if (LDS) {   // hand the accumulated impulses to the lattice kernels
     __syncthreads();
-    for (int hh = threadIdx.x; hh < lslots; hh += blockDim.x) {
-      const int key = lkeys[hh];
-      if (key < 0) continue;
-      const int g = table_insert(gkeys, mask, key, bs.err, gbits);
-      if (g < 0) continue;
-      for (int c = 0; c < 9; ++c) {
-        const long long v = lvals[(size_t)hh * 9 + c];
-        if (v) atomicAdd((unsigned long long*)&gvals[(size_t)g * SLOT_VALUES + 1 + c], (unsigned long long)v);
+    // (four slots of a thread at a time: the first probe of each, which finds
+    // most sites, is one round trip to the global table for all of them)
+    constexpr int AHEAD = 4;
+    for (int h0 = threadIdx.x; h0 < lslots; h0 += AHEAD * blockDim.x) {
+      int key[AHEAD], prev[AHEAD];
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        const int hh = h0 + u * blockDim.x;
+        key[u] = hh < lslots ? lkeys[hh] : -1;
+      }
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u)
+        prev[u] = key[u] < 0 ? 0 : ld_i32(&gkeys[hash_slot(key[u], gbits)]);
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        if (key[u] < 0) continue;
+        const int g = prev[u] == key[u] ? hash_slot(key[u], gbits)
+                                        : table_insert(gkeys, mask, key[u], bs.err, gbits);
+        if (g < 0) continue;
+        const long long* p = lvals + (size_t)(h0 + u * blockDim.x) * 9;
+        long long v[9];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) v[c] = p[c];
+        gn.add(g, v);
       }
     }
   }
