@@ -15,7 +15,8 @@
  *     charges (Eq. poisson), solved by red-black SOR with Chebyshev
  *     acceleration (Sec. II.C) or, EK_POISSON_MG, directly by Hartley
  *     transforms in the time loop (sides up to 960) and by red-black
- *     multigrid in stand-alone solves;
+ *     multigrid in stand-alone solves of boxes whose sides 4 divides, and in
+ *     every solve whose poisson_max_iter is below 20;
  *   - Langevin beads of a bead-spring chain coupled to the species by
  *     friction through a trilinear interpolation / spreading kernel, advanced
  *     with MD substeps (Sec. II.B, Eq. polymermodel);
@@ -386,7 +387,8 @@ ek_status ek_set_timing(struct ek_ctx* ctx, int32_t enable);
 ek_status ek_get_timing(struct ek_ctx* ctx, ek_timing* out);
 
 /* Launch modes (flags, both set by default).
- * EK_LAUNCH_GRAPHS: each multigrid V-cycle (EK_POISSON_MG), with or without
+ * EK_LAUNCH_GRAPHS: the time loop's direct solve, and each multigrid cycle of
+ * the solves that take those (EK_POISSON_MG), with or without
  *   its residual test, is recorded once as a HIP graph (on a stream the
  *   library creates; the caller's stream may be the default stream) and
  *   replayed on the context's stream; the graphs are recorded again when the

@@ -16,6 +16,7 @@ void launch_table_init(int* keys, long long* vals, hipStream_t s);
 void launch_table_init_bits(int* keys, long long* vals, int bits, hipStream_t s);
 size_t mg_workspace_bytes(int nx, int ny, int nz);
 size_t mg_sweep_bytes(int nx, int ny, int nz);
+size_t mg_direct_bytes(int nx, int ny, int nz);   // level 1's direct solver (0: none)
 
 // Tiles of the SOR that runs batches of iterations in one launch
 // (kernels_sor.hip), and its memory.
@@ -172,7 +173,8 @@ struct ek_ctx {
   ek_status learned_start(const double* b, double* x, ek::PoissonScalars* h);
   // Removes a pending mean from psi (before psi is read or ps reused).
   void settle_psi();
-  void mg_setup();
+  void mg_setup(char* direct_mem);
+  bool mg_coarsens() const;   // the box has a coarser level
   void mg_release();
   // One V-cycle; with norm_blocks given, its last finest-level sweep also
   // leaves the residual norms' block partials where the finest level allows

@@ -18,6 +18,17 @@
 //                residual, also zeroes the coarse iterate)
 //   prolongation trilinear cell-centred interpolation (weights 3/4, 1/4 per
 //                axis) added to the fine iterate
+// Where level 1 has a direct solver (sides up to 960: kernels_spectral.hip) it
+// is the coarsest level: three launches, and a coarse solution that is exact.
+// Swept, the coarsest level of a box that powers of two do not divide far took
+// most of the solve (120 x 120 x 200, coarsest 30 x 30 x 50: 600 launches and
+// 2.1 of its 3.1 ms), and the deeper hierarchies needed more cycles: to 1e-10
+// 16^3 takes 5 instead of 9 and 0.24 instead of 0.32 ms, 64^3 5 instead of 9
+// and 0.32 instead of 0.61 ms, 160 x 96 x 96 7 and 0.81 instead of 0.96 ms,
+// 200 x 120 x 120 5 instead of 6 and 1.2 instead of 3.1 ms.  (Two instead of
+// four pre-smoothing sweeps in the first cycle: 0 to 5 % less; none in the
+// later ones: 8 cycles.)  What follows is for the other boxes.
+//
 // A level is halved only while every side stays even (red-black colouring
 // needs even periodic sides).  The coarsest levels whose iterates and
 // right-hand sides fit in COARSE_LDS_BYTES of LDS run inside one workgroup
@@ -1119,7 +1130,7 @@ __global__ __launch_bounds__(1024) void k_coarse_cycle(LvlSet set, int first, Po
   for (int t = threadIdx.x; t < int(L[first].n); t += blockDim.x) set.l[first].x[t] = L[first].x[t];
 }
 
-// Cycle count of a V-cycle whose coarsest level is swept on the grid.
+// Cycle count of a cycle whose coarsest level takes launches of its own.
 __global__ void k_count_cycle(PoissonScalars* ps) {
   if (threadIdx.x == 0 && !ps->done) ps->cycles += 1;
 }
@@ -1137,6 +1148,7 @@ struct ek_ctx::MG {
   int coarsest_sweeps = COARSEST_SWEEPS;
   const double* pinv = nullptr;   // inverse for the direct coarsest solve, or null
   bool coarse_kernel = true;      // false: the coarsest level does not fit LDS
+  Spectral coarse;                // direct solver of level 1, then the coarsest (coarse.ok)
   // Full sweeps by k_sweep_z (out of place) on the launched levels whose tiles
   // fit: tile (sweep_tx, sweep_ty), sweep_nch chunks along z; 0 = half
   // sweeps.  The finest level sweeps into tmp0 and back, the others into tmp1.
@@ -1318,7 +1330,13 @@ static bool coarsest_inverse(const Lvl& C, std::vector<double>& inv) {
   return true;
 }
 
-void ek_ctx::mg_setup() {
+size_t ek::mg_direct_bytes(int nx, int ny, int nz) {
+  return halvable(nx, ny, nz) ? spectral_bytes(nx / 2, ny / 2, nz / 2) : 0;
+}
+
+bool ek_ctx::mg_coarsens() const { return mg && mg->levels.size() > 1; }
+
+void ek_ctx::mg_setup(char* direct_mem) {
   mg = new MG();
   int nx = p.nx, ny = p.ny, nz = p.nz;
   Lvl l0{nx, ny, nz, (long long)nx * ny * nz, 1.0, nullptr, nullptr};
@@ -1336,10 +1354,16 @@ void ek_ctx::mg_setup() {
     mem += 2 * b;
     mg->levels.push_back(l);
   }
+  if (direct_mem && mg->levels.size() > 1) {
+    const Lvl& l1 = mg->levels[1];
+    spectral_setup(mg->coarse, direct_mem, l1.nx, l1.ny, l1.nz, l1.h2);
+    if (mg->coarse.ok) mg->levels.resize(2);
+  }
   const int nl = (int)mg->levels.size();
   const Lvl& c = mg->levels.back();
   // LDS of the direct coarsest solve's inverse (reserved when it is planned)
-  const size_t inv_bytes = nl > 1 && c.n <= COARSEST_DIRECT_MAX ? (size_t)(c.n * c.n) * 8 : 0;
+  const bool inverse = nl > 1 && c.n <= COARSEST_DIRECT_MAX && !mg->coarse.ok;
+  const size_t inv_bytes = inverse ? (size_t)(c.n * c.n) * 8 : 0;
   int fc = nl - 1;
   size_t bytes = 16 * (size_t)mg->levels[fc].n;
   while (fc > 1 && bytes + 16 * (size_t)mg->levels[fc - 1].n <= COARSE_LDS_BYTES) {
@@ -1364,9 +1388,9 @@ void ek_ctx::mg_setup() {
   mg->first_coarse = fc;
   mg->coarse_lds = bytes;
   // a coarsest level too large for LDS is swept on the grid instead
-  mg->coarse_kernel = nl > 1 && fits(bytes);
+  mg->coarse_kernel = nl > 1 && !mg->coarse.ok && fits(bytes);
   // the coarsest level's inverse, after the levels in the workspace
-  if (nl > 1 && c.n <= COARSEST_DIRECT_MAX) {
+  if (inverse) {
     std::vector<double> inv;
     if (coarsest_inverse(c, inv) &&
         hipMemcpy(mem, inv.data(), inv.size() * 8, hipMemcpyHostToDevice) == hipSuccess)
@@ -1421,7 +1445,7 @@ void ek_ctx::mg_setup() {
       mg->sweep_nch[l] = sweep_chunks((long long)(L.nx / tx) * (L.ny / ty), L.nz, 1, 2, slots,
                                       mg->sweep_nch[l]);
     }
-    mg->fused0 = fc > 1 && mg->sweep_tx[0] == 64 && mg->sweep_ty[0] == 8 &&
+    mg->fused0 = (fc > 1 || mg->coarse.ok) && mg->sweep_tx[0] == 64 && mg->sweep_ty[0] == 8 &&
                  mg->levels[0].ny % ZR_TY == 0;
     if (mg->fused0) {
       // chunks of whole 2 x 2 x 2 blocks, h + 5 steps each, as many
@@ -1702,7 +1726,11 @@ ek_status ek_ctx::mg_vcycle(const double* bb, double* x, int* norm_blocks, bool 
     hipLaunchKernelGGL(k_restrict, level_launch(L[l + 1]).grid, level_launch(L[l + 1]).block, 0,
                        stream, F, L[l + 1], ps, l == 0 ? 1 : 0, omega_red);
   }
-  if (mg->coarse_kernel) {
+  if (mg->coarse.ok) {
+    launch_spectral_forward(mg->coarse, nullptr, L[1].f, ps, nullptr, stream);
+    launch_spectral_solve(mg->coarse, L[1].x, false, ps, stream);
+    hipLaunchKernelGGL(k_count_cycle, dim3(1), dim3(64), 0, stream, ps);
+  } else if (mg->coarse_kernel) {
     LvlSet set{};
     set.count = nl;
     for (int l = 0; l < nl; ++l) set.l[l] = L[l];

@@ -597,7 +597,7 @@ ek_status ek_ctx::spectral_solve(const double* bb, double* x, PoissonScalars h, 
   };
   while (!h.done && it < p.poisson_max_iter) {
     ++it;
-    hipGraphExec_t g = it == 1 && start_norms ? spectral_graph(bb, x) : nullptr;
+    hipGraphExec_t g = it == 1 && start_norms && !solo ? spectral_graph(bb, x) : nullptr;
     ek_status st = EK_OK;
     if (g) {
       const hipError_t e = hipGraphLaunch(g, stream);
