@@ -387,8 +387,8 @@ ek_status ek_set_timing(struct ek_ctx* ctx, int32_t enable);
 ek_status ek_get_timing(struct ek_ctx* ctx, ek_timing* out);
 
 /* Launch modes (flags, both set by default).
- * EK_LAUNCH_GRAPHS: the time loop's direct solve, and each multigrid cycle of
- * the solves that take those (EK_POISSON_MG), with or without
+ * EK_LAUNCH_GRAPHS: each multigrid cycle of the solves that take those
+ * (EK_POISSON_MG), with or without
  *   its residual test, is recorded once as a HIP graph (on a stream the
  *   library creates; the caller's stream may be the default stream) and
  *   replayed on the context's stream; the graphs are recorded again when the

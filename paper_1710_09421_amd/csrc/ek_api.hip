@@ -16,14 +16,6 @@ namespace {
 
 thread_local std::string g_create_error;
 
-#define EK_HIP(call)                                                                 \
-  do {                                                                               \
-    hipError_t e_ = (call);                                                          \
-    if (e_ != hipSuccess) {                                                          \
-      return ctx->fail(EK_EHIP, std::string(#call) + ": " + hipGetErrorString(e_));  \
-    }                                                                                \
-  } while (0)
-
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -290,17 +282,21 @@ ek_status ek_ctx::learned_start(const double* bb, double* x, PoissonScalars* h) 
   return initial_residual(bb, x, h);
 }
 
+// The time loop solves directly where the sides have a plan; a stand-alone
+// solve keeps the multigrid cycles, whose number its callers compare starts
+// by, unless the box has no coarser level (hundreds of SOR sweeps a cycle:
+// 100 x 90 x 30 to 1e-10 took 7.6 ms, direct 0.09).
+bool ek_ctx::direct_solve() const {
+  return p.poisson_method == EK_POISSON_MG && spec.ok && (!solo || !mg_coarsens()) &&
+         p.poisson_max_iter >= DIRECT_MIN_CYCLES;
+}
+
 ek_status ek_ctx::poisson(const double* bb, double* x, bool learned, int& iters, double& res,
                           double& res0) {
   PoissonScalars h{};
   last_fallback = 0;
   last_consulted = 0;
-  // the time loop solves directly where the sides have a plan; a stand-alone
-  // solve keeps the multigrid cycles, whose number its callers compare starts
-  // by, unless the box has no coarser level (hundreds of SOR sweeps a cycle:
-  // 100 x 90 x 30 to 1e-10 took 7.6 ms, direct 0.09)
-  const bool direct = p.poisson_method == EK_POISSON_MG && spec.ok &&
-                      (!solo || !mg_coarsens()) && p.poisson_max_iter >= DIRECT_MIN_CYCLES;
+  const bool direct = direct_solve();
   if (!learned && direct) return spectral_solve(bb, x, h, iters, res, res0, true);
   if (!learned && p.poisson_method == EK_POISSON_MG) {
     // the start's residual stays on the device (the cycles test its flag and
@@ -390,7 +386,59 @@ ek_status ek_ctx::step_impl(int n_steps) {
     int iters = 0;
     double res = 0, res0 = 0;
     defer_shift = held > 0 && !insulating();
-    ek_status st = poisson(b, psi, p.warm_start == EK_WS_LEARNED, iters, res, res0);
+    // What follows the solve.  `ahead`: enqueued before the host has seen the
+    // solve's result; the chain then skips itself unless that met the
+    // tolerance, everything else can be done again.
+    auto advance = [&](bool ahead) -> ek_status {
+      // beads: n_sub MD substeps with the fields of time t, friction spread
+      // (event 5: end of the chain kernel)
+      if (n_beads > 0) {
+        const ek_status bst = beads_advance<T>(overlap, timing ? events[6 * t + 5] : nullptr,
+                                               ahead ? ps : nullptr);
+        if (bst) return bst;
+      }
+      // events 3 and 4 are stamped by the fused kernel's own start and end.
+      // With the overlap it runs on the side stream from the box gather on,
+      // beside the chain (the longer of the two stays on the context stream,
+      // which then waits only for a lattice update that has long finished)
+      hipStream_t ls = stream;
+      if (overlap) {
+        EK_HIP(hipStreamWaitEvent(side_stream, side_fork, 0));
+        ls = side_stream;
+      }
+      launch_lb_step<T>((const T*)fcur(), (T*)fnext(), mask, psi, lp, bt, partials, nb_lb,
+                        overlap ? MASK_DEFER : 0u, dims, g, ls,
+                        timing ? events[6 * t + 3] : nullptr, timing ? events[6 * t + 4] : nullptr,
+                        npp, wvp);
+      if (overlap) {
+        // the box sites after the chain, beside the rest of the lattice update
+        // (disjoint sites and partials); their flags are cleared once both end
+        launch_lb_tail<T>((const T*)fcur(), (T*)fnext(), mask, psi, lp, bt, bead_origin(), n_beads,
+                          partials, nb_bulk, nb_lb, dims, stream, npp, wvp);
+        EK_HIP(hipEventRecord(side_join, side_stream));
+        EK_HIP(hipStreamWaitEvent(stream, side_join, 0));
+        launch_defer_clear(mask, bead_origin(), n_beads, dims, stream);
+      }
+      launch_sum_partials(partials, nb_lb, stats_dev, timing ? 1 : 0, stream,
+                          partials + 7LL * nb_lb, partials_cap - 7LL * nb_lb);
+      return EK_OK;
+    };
+    // The direct solve's one cycle almost always suffices: the rest of the
+    // step is enqueued behind it before the host waits for its result, so
+    // the device does not idle for the read-back (25 to 40 us a step).  The
+    // timers keep the phases apart.
+    const bool learned = p.warm_start == EK_WS_LEARNED;
+    const bool ahead = !timing && !learned && direct_solve();
+    ek_status st = EK_OK;
+    if (ahead) {
+      last_fallback = last_consulted = 0;
+      st = spectral_begin(b, psi);
+      if (!st) st = advance(true);
+    }
+    PoissonScalars h{};
+    if (!st)
+      st = ahead ? spectral_solve(b, psi, h, iters, res, res0, true, true)
+                 : poisson(b, psi, learned, iters, res, res0);
     defer_shift = false;
     if (st) return st;
     last_iters = iters;
@@ -399,36 +447,10 @@ ek_status ek_ctx::step_impl(int n_steps) {
     have_solve = true;
     if (timing) tacc.poisson_iters += iters;
     record(t, 2);
-    // beads: n_sub MD substeps with the fields of time t, friction spread
-    // (event 5: end of the chain kernel)
-    if (n_beads > 0) {
-      st = beads_advance<T>(overlap, timing ? events[6 * t + 5] : nullptr);
+    if (!ahead || iters > 1) {
+      st = advance(false);
       if (st) return st;
     }
-    // events 3 and 4 are stamped by the fused kernel's own start and end.
-    // With the overlap it runs on the side stream from the box gather on,
-    // beside the chain (the longer of the two stays on the context stream,
-    // which then waits only for a lattice update that has long finished)
-    hipStream_t ls = stream;
-    if (overlap) {
-      EK_HIP(hipStreamWaitEvent(side_stream, side_fork, 0));
-      ls = side_stream;
-    }
-    launch_lb_step<T>((const T*)fcur(), (T*)fnext(), mask, psi, lp, bt, partials, nb_lb,
-                      overlap ? MASK_DEFER : 0u, dims, g, ls,
-                      timing ? events[6 * t + 3] : nullptr, timing ? events[6 * t + 4] : nullptr,
-                      npp, wvp);
-    if (overlap) {
-      // the box sites after the chain, beside the rest of the lattice update
-      // (disjoint sites and partials); their flags are cleared once both end
-      launch_lb_tail<T>((const T*)fcur(), (T*)fnext(), mask, psi, lp, bt, bead_origin(), n_beads,
-                        partials, nb_bulk, nb_lb, dims, stream, npp, wvp);
-      EK_HIP(hipEventRecord(side_join, side_stream));
-      EK_HIP(hipStreamWaitEvent(stream, side_join, 0));
-      launch_defer_clear(mask, bead_origin(), n_beads, dims, stream);
-    }
-    launch_sum_partials(partials, nb_lb, stats_dev, timing ? 1 : 0, stream,
-                        partials + 7LL * nb_lb, partials_cap - 7LL * nb_lb);
     cur_is_a = !cur_is_a;
     ++step_count;
   }
@@ -549,12 +571,14 @@ ek_status ek_create(const ek_params* p, int32_t max_beads, void* dev_ws, size_t 
   c->bead_mem = ws + L.beads;
   c->mg_mem = ws + L.mg;
   c->mg_tmp = p->poisson_method == EK_POISSON_MG ? ws + L.mgt : nullptr;
-  if (hipHostMalloc(&c->pinned, 4096, hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(&c->pinned, 4096, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
     if (own) (void)hipFree(ws);
     delete c;
     g_create_error = "hipHostMalloc failed";
     return EK_EHIP;
   }
+  std::memset(c->pinned, 0, 4096);
+  c->look = (PoissonLook*)((char*)c->pinned + 2048);
   c->bx_sites = 0;
   c->bx_colour = 0;
   // the workspace arrives uninitialised: empty the bead node table and zero
@@ -603,7 +627,6 @@ void ek_destroy(ek_ctx* ctx) {
   if (ctx->side_join) (void)hipEventDestroy(ctx->side_join);
   for (hipEvent_t e : ctx->events) (void)hipEventDestroy(e);
   ctx->mg_release();
-  if (ctx->spec_graph) (void)hipGraphExecDestroy(ctx->spec_graph);
   delete ctx->net;
   if (ctx->pinned) (void)hipHostFree(ctx->pinned);
   if (ctx->own_ws) (void)hipFree(ctx->ws);

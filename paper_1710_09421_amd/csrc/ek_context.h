@@ -63,6 +63,15 @@ inline bool record_graph(hipStream_t stream, hipGraphExec_t* out, F enqueue) {
 // right-hand sides); a start closer than that is kept as it is.
 constexpr double LEARNED_GATE = 0.25;
 
+// A failing HIP call ends the caller with EK_EHIP and the call's text (`ctx`).
+#define EK_HIP(call)                                                                 \
+  do {                                                                               \
+    hipError_t e_ = (call);                                                          \
+    if (e_ != hipSuccess) {                                                          \
+      return ctx->fail(EK_EHIP, std::string(#call) + ": " + hipGetErrorString(e_));  \
+    }                                                                                \
+  } while (0)
+
 struct ek_ctx {
   ek_params p{};
   ek::Dims dims{};
@@ -187,16 +196,16 @@ struct ek_ctx {
                       bool first = false);
   bool mg_graphs(const double* b, double* x);
   // Direct solver of the time loop's periodic problem (spec.ok where the
-  // sides have a plan): one cycle, the solve, and its recorded first cycle.
+  // sides have a plan): one cycle, and the solve.
   ek::Spectral spec;
-  hipGraphExec_t spec_graph = nullptr;
-  const double* spec_graph_b = nullptr;
-  double* spec_graph_x = nullptr;
-  bool spec_graph_failed = false;
+  ek::PoissonLook* look = nullptr;   // the first cycle's result, in the pinned buffer
+  unsigned look_seq = 0;
   void spectral_cycle(const double* b, double* x, bool start);
-  hipGraphExec_t spectral_graph(const double* b, double* x);
+  bool direct_solve() const;        // a solve takes it
+  ek_status spectral_begin(const double* b, double* x);
+  ek_status spectral_look(ek::PoissonScalars& h);
   ek_status spectral_solve(const double* b, double* x, ek::PoissonScalars h, int& iters,
-                           double& res, double& res0, bool start_norms);
+                           double& res, double& res0, bool start_norms, bool begun = false);
   hipGraphExec_t mg_batch_graph(const double* b, double* x, int n, int untested, int opens);
   ek_status poisson(const double* b, double* x, bool learned, int& iters, double& res,
                     double& res0);
@@ -223,6 +232,8 @@ struct ek_ctx {
   // side_fork is recorded after the gather, for the lattice update that the
   // caller runs beside the chain on side_stream.
   template <typename T>
-  ek_status beads_advance(bool overlap, hipEvent_t chain_end);
+  // guard: launched ahead of the solve's result, the chain skips itself
+  // unless guard->done
+  ek_status beads_advance(bool overlap, hipEvent_t chain_end, const ek::PoissonScalars* guard);
   ek_status beads_check();
 };

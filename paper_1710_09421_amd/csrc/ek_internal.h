@@ -104,6 +104,13 @@ __device__ inline double mean_removed(double v, const PoissonScalars* ps, double
   return ps->zero_rhs ? 0.0 : __builtin_fma(-ps->psum, inv_n, v);
 }
 
+// The scalars as the device last wrote them to host memory: `seq`, stored
+// last, is the number of the write.
+struct PoissonLook {
+  PoissonScalars s;
+  unsigned seq;
+};
+
 // ---------------------------------------------------------------------------
 // Launchers (kernel files).  All take the stream as last argument.
 // ---------------------------------------------------------------------------
@@ -193,8 +200,10 @@ void launch_sor_half(double* psi, const double* b, const PoissonScalars* ps, int
 int residual_blocks(const Dims& d, const SiteGrid& g);
 int launch_residual(const double* psi, const double* b, PoissonScalars* ps, double* partials,
                     Dims d, const SiteGrid& g, hipStream_t s);
+// With `look` the scalars also go to host memory, write number seq.
 void launch_residual_final(const double* partials, int nblocks, double tol, int iter,
-                           int initial, PoissonScalars* ps, hipStream_t s);
+                           int initial, PoissonScalars* ps, hipStream_t s,
+                           PoissonLook* look = nullptr, unsigned seq = 0);
 void launch_psi_shift(double* psi, const PoissonScalars* ps, double inv_n, Dims d,
                       hipStream_t s);
 // Insulating walls: the same over the fluid sites only (the link words give

@@ -91,7 +91,8 @@ __global__ __launch_bounds__(256) void k_bead_box(BeadState bs, const T* __restr
 template <bool LDS, int TPB, int NBL, int MAXT, int WR, bool THERMAL>
 __global__ __launch_bounds__(MAXT) void k_md(BeadState bs, MDParams mp, int* gkeys,
                                              long long* gvals, uint32_t* mask, Dims d,
-                                             int gbits, int lds_slots) {
+                                             int gbits, int lds_slots, const PoissonScalars* ps) {
+  if (ps && !ps->done) return;   // launched ahead of a solve that needs another cycle
   extern __shared__ __align__(16) unsigned char smem[];
   md_chain<LDS, TPB, NBL, WR, THERMAL>(bs, mp, gkeys, gvals, mask, d, gbits, lds_slots, smem);
 }
@@ -165,7 +166,7 @@ ek_status ek_ctx::beads_deposit() {
 }
 
 template <typename T>
-ek_status ek_ctx::beads_advance(bool overlap, hipEvent_t chain_end) {
+ek_status ek_ctx::beads_advance(bool overlap, hipEvent_t chain_end, const PoissonScalars* guard) {
   BeadState bs = carve(bead_mem, max_beads < 1 ? 1 : max_beads);
   const LBParams lp = lb_params();
   const int wr = wall_reach(poly.sigma);
@@ -242,7 +243,7 @@ ek_status ek_ctx::beads_advance(bool overlap, hipEvent_t chain_end) {
     }
     if (slots < 1) return fail(EK_EHIP, "the chain's positions and pair lists do not fit LDS");
     hipLaunchKernelGGL(kernel, dim3(1), dim3(threads), lds, cs, bs, mp, keys, vals, mask, dims,
-                       HASH_BITS, slots);
+                       HASH_BITS, slots, guard);
     return EK_OK;
   };
   // the kernel instance for the chain's size, wall reach and bead noise (whose
@@ -265,8 +266,8 @@ ek_status ek_ctx::beads_advance(bool overlap, hipEvent_t chain_end) {
     return fail(EK_EHIP, "recording the chain timer failed");
   return EK_OK;
 }
-template ek_status ek_ctx::beads_advance<float>(bool, hipEvent_t);
-template ek_status ek_ctx::beads_advance<double>(bool, hipEvent_t);
+template ek_status ek_ctx::beads_advance<float>(bool, hipEvent_t, const PoissonScalars*);
+template ek_status ek_ctx::beads_advance<double>(bool, hipEvent_t, const PoissonScalars*);
 
 ek_status ek_ctx::beads_check() {
   BeadState bs = carve(bead_mem, max_beads < 1 ? 1 : max_beads);

@@ -204,29 +204,35 @@ int residual_zc(const Dims& d) {
 
 __global__ __launch_bounds__(1024) void k_residual_final(const double* __restrict__ partials,
                                                          int nblocks, double tol, int iter,
-                                                         int initial, PoissonScalars* ps) {
-  if (ps->done) return;
-  double t[3];
-  block_sums_1024<3>(partials, nblocks, t);
-  if (threadIdx.x == 0) {
-    if (iter < 0) iter = ps->cycles;   // counted on the device (replayed launches)
-    const double r2 = t[0], b2 = t[1];
-    double rel;
-    if (b2 > 0.0) rel = sqrt(r2 / b2);
-    else rel = r2 == 0.0 ? 0.0 : INFINITY;
-    ps->r2 = r2;
-    ps->b2 = b2;
-    ps->psum = t[2];
-    ps->rel = rel;
-    if (initial) ps->rel0 = rel;
-    if (b2 == 0.0) {
-      ps->zero_rhs = 1;
-      ps->done = 1;
-      ps->iters = iter;
-    } else if (rel <= tol) {
-      ps->done = 1;
-      ps->iters = iter;
+                                                         int initial, PoissonScalars* ps,
+                                                         PoissonLook* look, unsigned seq) {
+  if (!ps->done) {
+    double t[3];
+    block_sums_1024<3>(partials, nblocks, t);   // every thread has read the flag before it ends
+    if (threadIdx.x == 0) {
+      if (iter < 0) iter = ps->cycles;   // counted on the device (replayed launches)
+      const double r2 = t[0], b2 = t[1];
+      double rel;
+      if (b2 > 0.0) rel = sqrt(r2 / b2);
+      else rel = r2 == 0.0 ? 0.0 : INFINITY;
+      ps->r2 = r2;
+      ps->b2 = b2;
+      ps->psum = t[2];
+      ps->rel = rel;
+      if (initial) ps->rel0 = rel;
+      if (b2 == 0.0) {
+        ps->zero_rhs = 1;
+        ps->done = 1;
+        ps->iters = iter;
+      } else if (rel <= tol) {
+        ps->done = 1;
+        ps->iters = iter;
+      }
     }
+  }
+  if (look && threadIdx.x == 0) {
+    look->s = *ps;
+    __hip_atomic_store(&look->seq, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -410,10 +416,10 @@ int launch_residual(const double* psi, const double* b, PoissonScalars* ps, doub
   return nblocks;
 }
 
-void launch_residual_final(const double* partials, int nblocks, double tol, int iter,
-                           int initial, PoissonScalars* ps, hipStream_t s) {
+void launch_residual_final(const double* partials, int nblocks, double tol, int iter, int initial,
+                           PoissonScalars* ps, hipStream_t s, PoissonLook* look, unsigned seq) {
   hipLaunchKernelGGL(k_residual_final, dim3(1), dim3(1024), 0, s, partials, nblocks, tol, iter,
-                     initial, ps);
+                     initial, ps, look, seq);
 }
 
 void launch_psi_shift(double* psi, const PoissonScalars* ps, double inv_n, Dims d,

@@ -582,34 +582,54 @@ void ek_ctx::spectral_cycle(const double* bb, double* x, bool start) {
   launch_spectral_solve(spec, x, true, ps, stream);
 }
 
+// The first cycle, with the start's test, without waiting for its result.
+// That is written to host memory by the kernel that finds it: a copy of its
+// own and an event behind it left the device idle for 15 us.
+ek_status ek_ctx::spectral_begin(const double* bb, double* x) {
+  spectral_cycle(bb, x, true);
+  const int nr = residual_launch(bb, x);
+  launch_residual_final(partials, nr, p.poisson_tol, 1, 0, ps, stream, look, ++look_seq);
+  if (!defer_shift) launch_psi_shift(x, ps, 1.0 / double(dims.n), dims, stream);
+  return EK_OK;
+}
+
+// Waits for the result of spectral_begin's cycle.  Once the stream has ended
+// it is there; a failed stream ends the wait.
+ek_status ek_ctx::spectral_look(PoissonScalars& h) {
+  for (unsigned n = 1; __atomic_load_n(&look->seq, __ATOMIC_ACQUIRE) != look_seq; ++n) {
+    if (n % 1024 != 0) continue;
+    const hipError_t e = hipStreamQuery(stream);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess) return fail(EK_EHIP, std::string("hipStreamQuery: ") + hipGetErrorString(e));
+    if (__atomic_load_n(&look->seq, __ATOMIC_ACQUIRE) != look_seq)
+      return fail(EK_EHIP, "the solve's result did not arrive");
+  }
+  h = look->s;
+  return EK_OK;
+}
+
 // Cycles from the start x until the residual, taken by a pass of its own
 // after each, meets the tolerance.  With start_norms the first cycle also
-// tests the start (its residual is formed there anyway); the other kernels
-// of the solve skip themselves once the flag is set.  The first cycle and
-// its read-back are one recorded graph.
+// tests the start (its residual is formed there anyway; `begun`: it has been
+// enqueued); the other kernels of the solve skip themselves once the flag is
+// set.
 ek_status ek_ctx::spectral_solve(const double* bb, double* x, PoissonScalars h, int& iters,
-                                 double& res, double& res0, bool start_norms) {
+                                 double& res, double& res0, bool start_norms, bool begun) {
   int it = 0;
-  auto one = [&](bool start, int iter) {
-    spectral_cycle(bb, x, start);
-    const int nr = residual_launch(bb, x);
-    launch_residual_final(partials, nr, p.poisson_tol, iter, 0, ps, stream);
-  };
+  ek_status st = EK_OK;
+  if (start_norms) {
+    if (!begun) st = spectral_begin(bb, x);
+    if (!st) st = spectral_look(h);
+    if (st) return st;
+    it = 1;
+  }
   while (!h.done && it < p.poisson_max_iter) {
     ++it;
-    hipGraphExec_t g = it == 1 && start_norms && !solo ? spectral_graph(bb, x) : nullptr;
-    ek_status st = EK_OK;
-    if (g) {
-      const hipError_t e = hipGraphLaunch(g, stream);
-      if (e != hipSuccess) return fail(EK_EHIP, std::string("hipGraphLaunch: ") + hipGetErrorString(e));
-      st = sync();
-      if (st) return st;
-      std::memcpy(&h, pinned, sizeof(PoissonScalars));
-    } else {
-      one(start_norms && it == 1, it);
-      st = read_scalars(&h);
-      if (st) return st;
-    }
+    spectral_cycle(bb, x, false);
+    const int nr = residual_launch(bb, x);
+    launch_residual_final(partials, nr, p.poisson_tol, it, 0, ps, stream);
+    st = read_scalars(&h);
+    if (st) return st;
   }
   res0 = h.rel0;
   res = h.rel;
@@ -622,36 +642,6 @@ ek_status ek_ctx::spectral_solve(const double* bb, double* x, PoissonScalars h, 
   }
   iters = h.iters;
   if (defer_shift) shift_pending = true;
-  else launch_psi_shift(x, ps, 1.0 / double(dims.n), dims, stream);
+  else if (!start_norms || it > 1) launch_psi_shift(x, ps, 1.0 / double(dims.n), dims, stream);
   return EK_OK;
-}
-
-hipGraphExec_t ek_ctx::spectral_graph(const double* bb, double* x) {
-  if (!graph_launch || spec_graph_failed) return nullptr;
-  if (spec_graph && spec_graph_b == bb && spec_graph_x == x) return spec_graph;
-  if (spec_graph) (void)hipGraphExecDestroy(spec_graph);
-  spec_graph = nullptr;
-  const hipStream_t own = stream;
-  hipStream_t rec = nullptr;
-  if (hipStreamCreateWithFlags(&rec, hipStreamNonBlocking) != hipSuccess) {
-    (void)hipGetLastError();
-    spec_graph_failed = true;
-    return nullptr;
-  }
-  stream = rec;   // the launchers enqueue on `stream`
-  const bool ok = record_graph(rec, &spec_graph, [&] {
-    spectral_cycle(bb, x, true);
-    const int nr = residual_launch(bb, x);
-    launch_residual_final(partials, nr, p.poisson_tol, 1, 0, ps, stream);
-    (void)hipMemcpyAsync(pinned, ps, sizeof(PoissonScalars), hipMemcpyDeviceToHost, stream);
-  });
-  stream = own;
-  (void)hipStreamDestroy(rec);
-  if (!ok) {
-    spec_graph_failed = true;
-    return nullptr;
-  }
-  spec_graph_b = bb;
-  spec_graph_x = x;
-  return spec_graph;
 }
