@@ -332,6 +332,18 @@ void ek_ctx::record(int t, int k) {
 
 template <typename T>
 ek_status ek_ctx::step_impl(int n_steps) {
+  const ek_status st = step_loop<T>(n_steps);
+  clear_defer();   // of a call that ended early
+  return st;
+}
+
+void ek_ctx::clear_defer() {
+  if (defer_set) launch_defer_clear(mask, bead_origin(), n_beads, dims, stream);
+  defer_set = false;
+}
+
+template <typename T>
+ek_status ek_ctx::step_loop(int n_steps) {
   ek_ctx* ctx = this;
   const SiteGrid g = bx_sites ? site_grid(p.nx, p.ny, p.nz, bx_sites) : lattice_grid(p.nx, p.ny, p.nz);
   const int nb = g.nblocks();
@@ -417,10 +429,13 @@ ek_status ek_ctx::step_impl(int n_steps) {
                           partials, nb_bulk, nb_lb, dims, stream, npp, wvp);
         EK_HIP(hipEventRecord(side_join, side_stream));
         EK_HIP(hipStreamWaitEvent(stream, side_join, 0));
-        launch_defer_clear(mask, bead_origin(), n_beads, dims, stream);
+        defer_set = true;
       }
-      launch_sum_partials(partials, nb_lb, stats_dev, timing ? 1 : 0, stream,
-                          partials + 7LL * nb_lb, partials_cap - 7LL * nb_lb);
+      // the sums are read after the last step only (the timers count sites in
+      // every step)
+      if (timing || t == n_steps - 1)
+        launch_sum_partials(partials, nb_lb, stats_dev, timing ? 1 : 0, stream,
+                            partials + 7LL * nb_lb, partials_cap - 7LL * nb_lb);
       return EK_OK;
     };
     // The direct solve's one cycle almost always suffices: the rest of the
@@ -454,6 +469,7 @@ ek_status ek_ctx::step_impl(int n_steps) {
     cur_is_a = !cur_is_a;
     ++step_count;
   }
+  clear_defer();   // the last step's boxes; the others were cleared with the node table
   ek_status st = sync();
   if (st) return st;
   if (timing) {

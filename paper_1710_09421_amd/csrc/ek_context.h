@@ -201,6 +201,7 @@ struct ek_ctx {
   ek::PoissonLook* look = nullptr;   // the first cycle's result, in the pinned buffer
   unsigned look_seq = 0;
   void spectral_cycle(const double* b, double* x, bool start);
+  bool defer_set = false;           // the last step's boxes are still flagged MASK_DEFER
   bool direct_solve() const;        // a solve takes it
   ek_status spectral_begin(const double* b, double* x);
   ek_status spectral_look(ek::PoissonScalars& h);
@@ -222,6 +223,9 @@ struct ek_ctx {
   int psi_hist = 0;
   template <typename T>
   ek_status step_impl(int n_steps);
+  template <typename T>
+  ek_status step_loop(int n_steps);
+  void clear_defer();               // clears the flags of defer_set
 
   // beads (kernels_md.hip)
   ek::BeadTableView bead_view() const;

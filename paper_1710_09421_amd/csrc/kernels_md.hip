@@ -71,6 +71,19 @@ __global__ __launch_bounds__(256) void k_table_clear(int* keys, long long* vals,
                     gridDim.x * blockDim.x);
 }
 
+// The same, with the last step's box flags (item = bead, node of its box).
+__global__ __launch_bounds__(256) void k_chain_clear(int* keys, long long* vals, uint32_t* mask,
+                                                     Dims d, int bits,
+                                                     const int* __restrict__ origin, int n_beads) {
+  const int tid = blockIdx.x * blockDim.x + threadIdx.x, nthreads = gridDim.x * blockDim.x;
+  table_clear_items(keys, vals, mask, d.n, bits, tid, nthreads);
+  for (int item = tid; item < n_beads * BOX3; item += nthreads) {
+    const int i = item / BOX3, t = item % BOX3;
+    atomicAnd(&mask[site_of(origin[3 * i] + t % BOX, origin[3 * i + 1] + (t / BOX) % BOX,
+                            origin[3 * i + 2] + t / (BOX * BOX), d)], ~MASK_DEFER);
+  }
+}
+
 __global__ __launch_bounds__(256) void k_deposit(BeadState bs, int n, int* keys, long long* vals,
                                                  uint32_t* mask, Dims d, int bits, int fluid_only) {
   deposit_items(bs, n, keys, vals, mask, d, bits, blockIdx.x * blockDim.x + threadIdx.x,
@@ -159,7 +172,12 @@ BeadTableView ek_ctx::bead_view() const {
 
 ek_status ek_ctx::beads_deposit() {
   BeadState bs = carve(bead_mem, max_beads < 1 ? 1 : max_beads);
-  launch_table_clear(keys, vals, mask, dims.n, stream);
+  if (defer_set)
+    hipLaunchKernelGGL(k_chain_clear, dim3(HASH_SLOTS / 256), dim3(256), 0, stream, keys, vals, mask,
+                       dims, HASH_BITS, bs.origin, n_beads);
+  else
+    launch_table_clear(keys, vals, mask, dims.n, stream);
+  defer_set = false;
   hipLaunchKernelGGL(k_deposit, dim3((8 * n_beads + 255) / 256), dim3(256), 0, stream, bs, n_beads,
                      keys, vals, mask, dims, HASH_BITS, insulating() ? 1 : 0);
   return EK_OK;
