@@ -6,23 +6,27 @@
 // half sweep and two per residual test are bound by their launches and by the
 // caches' latency (17 us an iteration, 22 with insulating walls).  Here
 // a workgroup owns a tile of whole x-rows (ty rows by tz planes) for a whole
-// batch; after each half sweep it sends the new values of its boundary rows to
-// its four neighbours and takes theirs, which costs about one trip through
-// the memory side of the chip per half sweep. Measured: 3.0 us an iteration
-// at 64x64x128 (256 tiles of 4 x 8 rows); a solve to 1e-8 from zero 6.93 ->
-// 1.62 ms, a step of the 48x48x64 insulating pore 16.6 -> 3.3 ms, a step of
-// the 32^3 box to 1e-10 1.76 -> 0.69 ms.
+// batch, and what bounds it is the trip of its boundary rows through the
+// memory side of the chip to its neighbours.  There is one such trip an
+// iteration: a workgroup also relaxes the red sites of the ring around its
+// tile, for which it needs the black values of two rings, and after the black
+// half sweep it takes those from its eight neighbours.  (Sending each colour's
+// ring after its half sweep relaxes nothing twice but makes two trips: 3.1
+// instead of 1.95 us an iteration at 32^3, 3.6 instead of 2.25 at 64^3, 3.9
+// instead of 2.9 at 64x64x128.)  A solve of 64x64x128 to 1e-8 from zero takes
+// 1.4 ms (6.9 by single launches), a step of the 48x48x64 insulating pore 2.2
+// (16.6), a step of the 32^3 box to 1e-10 0.56 (1.76).
 //
 // Exchange: every value travels as one 64-bit device-scope store into a slot
-// of the sender's mailbox; the receiver polls the slot itself until it no
+// of the receiver's mailbox; the receiver polls the slot itself until it no
 // longer holds EMPTY (a NaN no arithmetic produces), then empties it again.
 // No flag follows the data and no fence is needed: a slot is one word, and
-// nothing else is read because of it.  Half sweep g uses slot set g & 3.  A
-// set is written again four half sweeps later, by when its reader has emptied
-// it: the reader's polling wait of half sweep g + 2 also waits for the stores
-// that emptied set g, and the sender cannot be at half sweep g + 4 before it
-// has received what the reader sent after that.  All values sent are taken
-// before a launch ends, so the mailboxes are empty between launches.
+// nothing else is read because of it.  Iteration g uses slot set g & 3.  A set
+// is written again four iterations later, by when its reader has emptied it:
+// the reader's polling wait of iteration g + 2 also waits for the stores that
+// emptied set g, and the sender cannot send in iteration g + 4 before it has
+// received what the reader sent after that.  All values sent are taken before
+// a launch ends, so the mailboxes are empty between launches.
 //
 // The launch is cooperative, so every workgroup it waits for is resident; a
 // wait is bounded all the same (the solve then fails, and the context takes
@@ -54,11 +58,12 @@ constexpr unsigned long long EMPTY = 0xFFF7A5C35A3C7F11ull;
 constexpr int SLOTS = 4;
 constexpr int SOR_THREADS = 512;
 constexpr int SOR_WAVES = SOR_THREADS / 64;
-constexpr int SOR_MAX_BATCH = 64;
+constexpr int SOR_MAX_BATCH = 256;
 constexpr int SOR_NEAR = 12;          // iterations left within which a batch crosses the end
 constexpr int SOR_SHORT = 4;          // else it stops this many before the expected end
 constexpr int SOR_MAX_ITEMS = 4;      // sites of a colour per thread
-constexpr int SOR_MAX_TAKE = 4;       // face values a thread takes per half sweep
+constexpr int sor_take(int u) { return u == 1 ? 4 : 8; }   // values a thread takes per iteration
+constexpr int SOR_MAX_TAKE = sor_take(SOR_MAX_ITEMS);
 constexpr int SOR_MAX_GROUPS = 256;   // one workgroup per compute unit
 constexpr size_t SOR_LDS_MAX = 150 * 1024;
 constexpr int SOR_SPIN_LIMIT = 1 << 20;
@@ -99,6 +104,22 @@ struct SorArgs {
 
 __device__ __forceinline__ bool tested(const SorArgs& a, int it) {
   return it % a.every == 0 || it == a.max_iter;
+}
+
+// The relaxation factors' recursion, rounded as the host rounds it (no fused
+// multiply-add).
+__device__ inline double chebyshev_first(double rj) {
+#pragma clang fp contract(off)
+  const double h = 0.5 * rj;
+  const double t = h * rj;
+  return 1.0 / (1.0 - t);
+}
+__device__ inline double chebyshev_next(double rj, double omega) {
+#pragma clang fp contract(off)
+  const double q = 0.25 * rj;
+  const double t = q * rj;
+  const double v = t * omega;
+  return 1.0 / (1.0 - v);
 }
 
 // What this launch runs, from what the last one left: base, n, cur and omega
@@ -169,10 +190,11 @@ __device__ inline SorControl sor_verdict(const SorArgs& a, double* rel) {
 
 // NEU: insulating walls (fluid sites only, the link words' bits 1..6 mark the
 // solid face neighbours, see kernels_poisson.hip).  U: sites of a colour per
-// thread.
+// thread, of the tile and of its ring.  Colour 0 is red here, colour 1 black.
 template <bool NEU, int U>
 __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
-  extern __shared__ double P[];      // [colour][row of the tile and its ring][x / 2]
+  extern __shared__ double P[];      // [colour][row of the tile and two rings][x / 2]
+  constexpr int TAKE = sor_take(U);
   __shared__ int s_abort;
   __shared__ double s_rel[SOR_MAX_BATCH];
   __shared__ double s_sum[SOR_WAVES];
@@ -183,35 +205,53 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
   }
   const int n_it = c.n;
   const int tid = threadIdx.x, w = blockIdx.x, W = gridDim.x;
-  const int ty = a.ty, tz = a.tz, hx = a.nx / 2, ry = ty + 2;
-  const int plane = ry * (tz + 2) * hx;
+  const int ty = a.ty, tz = a.tz, hx = a.nx / 2, ry = ty + 4;
+  const int plane = ry * (tz + 4) * hx;
   const int wy = w % a.gy, wz = w / a.gy, y0 = wy * ty, z0 = wz * tz;
   const double* in = a.buf[c.cur];
   double* out = a.buf[c.cur ^ 1];
   const double shift = a.ps->shift;
   if (tid == 0) s_abort = 0;
-  // the tile and its ring (the ring's corner rows are never read)
-  for (int t = tid; t < ry * (tz + 2) * a.nx; t += SOR_THREADS) {
+  // LDS index of row (yy, zz) of the tile, rings at -2, -1 and ty, ty + 1
+  auto row_at = [&](int yy, int zz) { return ((zz + 2) * ry + yy + 2) * hx; };
+  // the tile and its rings (of the corners only the inner rows are read)
+  for (int t = tid; t < ry * (tz + 4) * a.nx; t += SOR_THREADS) {
     const int row = t / a.nx, x = t - row * a.nx;
-    const int zz = row / ry - 1, yy = row % ry - 1;
+    const int zz = row / ry - 2, yy = row % ry - 2;
     const int y = (y0 + yy + a.ny) % a.ny, z = (z0 + zz + a.nz) % a.nz;
     P[((x + y + z) & 1) * plane + row * hx + (x >> 1)] =
         in[((long long)z * a.ny + y) * a.nx + x];
   }
   // this thread's sites: rows on the tile's faces first, so that what the
   // neighbours wait for is sent before the inner rows are relaxed
-  const int rows = ty * tz, items = rows * hx;
-  const int ez = tz > 1 ? 2 : 1, ey = ty > 1 ? 2 : 1, mid = max(tz - 2, 0), inner = max(ty - 2, 0);
-  const int face_items = (ez * ty + mid * ey) * hx;
-  int own[U], yz[U], odd[U];         // LDS index; yy | zz << 16; x of colour 0 = 2 i + odd
-  double rhs[2][U];
-  int open[2][U];                    // NEU: bits 1..6 open neighbours, bit 0 fluid
+  const int rows = ty * tz, items = rows * hx, ring_items = 2 * (ty + tz) * hx;
+  // LDS index o of a site, and o2 of the neighbour in x that is not at o in the
+  // other colour's array
+  int own[U], own2[2][U], yz[U];     // yz: yy | zz << 16
+  int ring[U], ring2[U];             // the red sites of the ring that it relaxes too
+  double rhs[2][U], ring_rhs[U];
+  int open[2][U], ring_open[U];      // NEU: bits 1..6 open neighbours (1 at o, 2 at o2), bit 0 fluid
+  auto beside = [&](int o, int i, bool right) {   // right: x = 2 i + 1
+    return right ? (i == hx - 1 ? o - hx + 1 : o + 1) : (i == 0 ? o + hx - 1 : o - 1);
+  };
+  auto site_of = [&](int yy, int zz, int x) {
+    const int y = (y0 + yy + a.ny) % a.ny, z = (z0 + zz + a.nz) % a.nz;
+    return ((long long)z * a.ny + y) * a.nx + x;
+  };
+  auto neighbours_of = [&](long long s, bool right) {
+    if constexpr (NEU) {
+      const uint32_t m = a.mask[s];
+      const int n = int(~m & 126u) | (m & MASK_SOLID ? 0 : 1);   // bit 1: x - 1, bit 2: x + 1
+      return right ? n : (n & ~6) | (n & 2) << 1 | (n & 4) >> 1;
+    } else {
+      return 127;
+    }
+  };
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int t = min(tid + u * SOR_THREADS, items - 1);
-    int r = t / hx;
-    const int i = t - r * hx;
-    int yy, zz;
+    const int ez = 2, ey = 2, mid = tz - 2, inner = max(ty - 2, 1);
+    int t = min(tid + u * SOR_THREADS, items - 1);
+    int r = t / hx, i = t - r * hx, yy, zz;
     if (r < ez * ty) {
       zz = r < ty ? 0 : tz - 1;
       yy = r % ty;
@@ -220,112 +260,136 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
       yy = r % ey ? ty - 1 : 0;
     } else {
       r -= mid * ey;
-      zz = 1 + r / max(inner, 1);
-      yy = 1 + r % max(inner, 1);
+      zz = 1 + r / inner;
+      yy = 1 + r % inner;
     }
-    own[u] = ((zz + 1) * ry + yy + 1) * hx + i;
+    own[u] = row_at(yy, zz) + i;
     yz[u] = yy | zz << 16;
-    odd[u] = (y0 + yy + z0 + zz) & 1;
+    int odd = (y0 + yy + z0 + zz) & 1;           // x of red = 2 i + odd
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
-      const int x = 2 * i + (odd[u] ^ k);
-      const long long s = ((long long)(z0 + zz) * a.ny + y0 + yy) * a.nx + x;
+      const long long s = site_of(yy, zz, 2 * i + (odd ^ k));
+      own2[k][u] = beside(own[u], i, (odd ^ k) != 0);
       rhs[k][u] = a.b[s] + shift;
-      open[k][u] = 127;
-      if constexpr (NEU) {
-        const uint32_t m = a.mask[s];
-        open[k][u] = int(~m & 126u) | (m & MASK_SOLID ? 0 : 1);
-      }
+      open[k][u] = neighbours_of(s, (odd ^ k) != 0);
     }
+    t = min(tid + u * SOR_THREADS, ring_items - 1);
+    r = t / hx;
+    i = t - r * hx;
+    if (r < 2 * tz) {
+      yy = r < tz ? -1 : ty;
+      zz = r % tz;
+    } else {
+      r -= 2 * tz;
+      zz = r < ty ? -1 : tz;
+      yy = r % ty;
+    }
+    // sides are even: a wrap keeps the colours
+    ring[u] = row_at(yy, zz) + i;
+    odd = (y0 + yy + z0 + zz) & 1;
+    const long long s = site_of(yy, zz, 2 * i + odd);
+    ring2[u] = beside(ring[u], i, odd != 0);
+    ring_rhs[u] = a.b[s] + shift;
+    ring_open[u] = neighbours_of(s, odd != 0);
   }
-  // face values this thread takes: slot in the sender's mailbox, LDS target
-  const int face = 2 * (ty + tz) * hx;
-  int src[SOR_MAX_TAKE], dst[SOR_MAX_TAKE];
-  unsigned long long* send = a.mail + (size_t)w * face;
-  const size_t set = (size_t)W * face;
+  // The black values this workgroup takes after every iteration, by rows of
+  // its mailbox: 2 tz rows below and above in y (yy = -1 - d and ty + d at
+  // d tz + zz), 2 ty rows below and above in z, four corner rows.
+  const int box_rows = 4 * (ty + tz) + 4, box = box_rows * hx;
+  const size_t set = (size_t)W * box;
+  int dst[TAKE];             // LDS index, or -1
 #pragma unroll
-  for (int v = 0; v < SOR_MAX_TAKE; ++v) {
+  for (int v = 0; v < TAKE; ++v) {
     const int t = tid + v * SOR_THREADS;
-    src[v] = -1;
-    dst[v] = 0;
-    if (t >= face) continue;
-    int k = t / hx;
+    dst[v] = -1;
+    if (t >= box) continue;
+    int k = t / hx, yy, zz;
     const int i = t - k * hx;
-    int from, row, slot;
-    if (k < tz) {                    // below in y: its face 1
-      from = wz * a.gy + (wy == 0 ? a.gy - 1 : wy - 1);
-      slot = (tz + k) * hx + i;
-      row = (k + 1) * ry;
-    } else if ((k -= tz) < tz) {     // above in y: its face 0
-      from = wz * a.gy + (wy == a.gy - 1 ? 0 : wy + 1);
-      slot = k * hx + i;
-      row = (k + 1) * ry + ty + 1;
-    } else if ((k -= tz) < ty) {     // below in z: its face 3
-      from = (wz == 0 ? a.gz - 1 : wz - 1) * a.gy + wy;
-      slot = (2 * tz + ty + k) * hx + i;
-      row = k + 1;
-    } else {                         // above in z: its face 2
-      k -= ty;
-      from = (wz == a.gz - 1 ? 0 : wz + 1) * a.gy + wy;
-      slot = (2 * tz + k) * hx + i;
-      row = (tz + 1) * ry + k + 1;
+    if (k < 2 * tz) {
+      yy = -1 - k / tz;
+      zz = k % tz;
+    } else if ((k -= 2 * tz) < 2 * tz) {
+      yy = ty + k / tz;
+      zz = k % tz;
+    } else if ((k -= 2 * tz) < 2 * ty) {
+      zz = -1 - k / ty;
+      yy = k % ty;
+    } else if ((k -= 2 * ty) < 2 * ty) {
+      zz = tz + k / ty;
+      yy = k % ty;
+    } else {
+      k -= 2 * ty;
+      yy = k & 1 ? ty : -1;
+      zz = k & 2 ? tz : -1;
     }
-    src[v] = from * face + slot;
-    dst[v] = row * hx + i;
+    dst[v] = row_at(yy, zz) + i;
   }
-  // takes the values sent in half sweep g (colour g & 1) into the ring
-  auto take = [&](int g) {
-    unsigned long long* box = a.mail + (g & (SLOTS - 1)) * set;
-    unsigned long long v[SOR_MAX_TAKE];
+  // the mailboxes of the eight neighbours
+  const int wyl = wy == 0 ? a.gy - 1 : wy - 1, wyh = wy == a.gy - 1 ? 0 : wy + 1;
+  const int wzl = wz == 0 ? a.gz - 1 : wz - 1, wzh = wz == a.gz - 1 ? 0 : wz + 1;
+  auto mail_of = [&](int y, int z) { return a.mail + (size_t)(z * a.gy + y) * box; };
+  unsigned long long* const mine = mail_of(wy, wz);
+  // takes the values sent after iteration it into the rings
+  auto take = [&](int it) {
+    unsigned long long* from = mine + (it & (SLOTS - 1)) * set + tid;
+    unsigned long long v[TAKE];
     int spins = 0;
     bool all;
+    // The values cannot be there before a trip through the memory side; a
+    // look before that comes back empty only after the next could have come
+    // back full (64^3: 2.7 us an iteration without the pause of 512 clocks,
+    // 2.25 with it, 2.4 and 2.6 with twice and three times as long a one).
+    __builtin_amdgcn_s_sleep(8);
     do {
       all = true;
 #pragma unroll
-      for (int k = 0; k < SOR_MAX_TAKE; ++k) v[k] = 0;
+      for (int k = 0; k < TAKE; ++k) v[k] = 0;
 #pragma unroll
-      for (int k = 0; k < SOR_MAX_TAKE; ++k)
-        if (src[k] >= 0)
-          v[k] = __hip_atomic_load(box + src[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int k = 0; k < TAKE; ++k)
+        if (dst[k] >= 0)
+          v[k] = __hip_atomic_load(from + k * SOR_THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-      for (int k = 0; k < SOR_MAX_TAKE; ++k) all = all && v[k] != EMPTY;
+      for (int k = 0; k < TAKE; ++k) all = all && v[k] != EMPTY;
       if (!all && ++spins > SOR_SPIN_LIMIT) {
         s_abort = 1;
         break;
       }
     } while (!all);
 #pragma unroll
-    for (int k = 0; k < SOR_MAX_TAKE; ++k)
-      if (src[k] >= 0) {
-        P[(g & 1) * plane + dst[k]] = __longlong_as_double((long long)v[k]);
-        __hip_atomic_store(box + src[k], EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int k = 0; k < TAKE; ++k)
+      if (dst[k] >= 0) {
+        P[plane + dst[k]] = __longlong_as_double((long long)v[k]);
+        __hip_atomic_store(from + k * SOR_THREADS, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
   };
   const double rj = a.rj;
-  double omega = c.omega;
-  bool first = c.base == 0;
+  // this iteration's factors of red and black; the next ones are computed
+  // while the neighbours' values are on their way
+  double omega = c.omega, omega_black;
+  omega_black = c.base == 0 ? chebyshev_first(rj) : chebyshev_next(rj, omega);
   double acc = 0.0;
-  // sum over the face neighbours of site u of colour k (the other colour)
-  auto around = [&](int k, int u) -> double {
+  // sum over the face neighbours (of the other colour) of the site of colour
+  // k at LDS index o; the two in x commute
+  auto around = [&](int k, int o, int o2, int m) -> double {
     const double* q = P + (k ^ 1) * plane;
-    const int o = own[u], i = o % hx;
-    const bool right = (odd[u] ^ k) != 0;       // x = 2 i + 1
-    const double xm = q[right ? o : (i == 0 ? o + hx - 1 : o - 1)];
-    const double xp = q[right ? (i == hx - 1 ? o - hx + 1 : o + 1) : o];
+    const double x1 = q[o], x2 = q[o2];
     const double ym = q[o - hx], yp = q[o + hx], zm = q[o - ry * hx], zp = q[o + ry * hx];
     if constexpr (NEU) {
-      const int m = open[k][u];
       double s = 0.0;
-      s += m & 2 ? xm : 0.0;
-      s += m & 4 ? xp : 0.0;
+      s += m & 2 ? x1 : 0.0;
+      s += m & 4 ? x2 : 0.0;
       s += m & 8 ? ym : 0.0;
       s += m & 16 ? yp : 0.0;
       s += m & 32 ? zm : 0.0;
       s += m & 64 ? zp : 0.0;
       return s;
     } else {
-      return xm + xp + ym + yp + zm + zp;
+      return x1 + x2 + ym + yp + zm + zp;
     }
+  };
+  auto relaxed = [&](double w_sor, double old, double s, double f, int m) {
+    if constexpr (NEU) return old + w_sor * ((s - f) / double(__builtin_popcount(m & 126)) - old);
+    else return old + w_sor * ((s - f) * (1.0 / 6.0) - old);
   };
   // squared residual at a site with neighbour sum s and value v
   auto square = [&](int k, int u, double s, double v) {
@@ -354,59 +418,73 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
       for (int k = 0; k < 2; ++k)
         __hip_atomic_store(&a.ctl[k].aborted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
+  bool test = false;
+  int since = c.base % a.every;          // iterations since the last multiple of `every`
   for (int it = 1; it <= n_it; ++it) {
-    const bool test = tested(a, c.base + it), prev = it > 1 && tested(a, c.base + it - 1);
+    const bool prev = test;
+    since = since + 1 == a.every ? 0 : since + 1;
+    test = since == 0 || c.base + it == a.max_iter;
+    if (it > 1) take(it - 1);
+    __syncthreads();
+    if (s_abort) return give_up();
+    // red, in the tile and in the ring around it
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int g = 2 * (it - 1) + k;
-      if (g > 0) take(g - 1);
-      __syncthreads();
-      if (s_abort) return give_up();
-      if (k == 1 && prev) store_part(it - 1);
-      unsigned long long* box = send + (g & (SLOTS - 1)) * set;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int t = tid + u * SOR_THREADS;
-        if (t >= items) continue;
-        double* p = P + k * plane + own[u];
-        const double old = *p;
-        double v = old;
-        if (!NEU || (open[k][u] & 1)) {
-          const double s = around(k, u);
-          if (k == 0 && prev) acc += square(k, u, s, old);
-          if constexpr (NEU)
-            v = old + omega * ((s - rhs[k][u]) / double(__builtin_popcount(open[k][u] & 126)) - old);
-          else
-            v = old + omega * ((s - rhs[k][u]) * (1.0 / 6.0) - old);
-          if (k == 1 && test) acc += square(k, u, s, v);
-          *p = v;
-        }
-        if (t < face_items) {
-          const int yy = yz[u] & 0xffff, zz = yz[u] >> 16, i = own[u] % hx;
-          unsigned long long m = (unsigned long long)__double_as_longlong(v);
-          if (m == EMPTY) m ^= 1;
-          auto put = [&](int slot) {
-            __hip_atomic_store(box + slot, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          };
-          if (yy == 0) put(zz * hx + i);
-          if (yy == ty - 1) put((tz + zz) * hx + i);
-          if (zz == 0) put((2 * tz + yy) * hx + i);
-          if (zz == tz - 1) put((2 * tz + ty + yy) * hx + i);
-        }
+    for (int u = 0; u < U; ++u) {
+      if (tid + u * SOR_THREADS < items && (!NEU || (open[0][u] & 1))) {
+        double* p = P + own[u];
+        const double old = *p, s = around(0, own[u], own2[0][u], open[0][u]);
+        if (prev) acc += square(0, u, s, old);
+        *p = relaxed(omega, old, s, rhs[0][u], open[0][u]);
       }
-      if (k == 0 && prev) sum_waves();
-      omega = first ? 1.0 / (1.0 - 0.5 * rj * rj) : 1.0 / (1.0 - 0.25 * rj * rj * omega);
-      first = false;
+      if (tid + u * SOR_THREADS < ring_items && (!NEU || (ring_open[u] & 1))) {
+        double* p = P + ring[u];
+        *p = relaxed(omega, *p, around(0, ring[u], ring2[u], ring_open[u]), ring_rhs[u], ring_open[u]);
+      }
     }
+    if (prev) sum_waves();
+    __syncthreads();
+    if (prev) store_part(it - 1);
+    // black, and to the neighbours
+    const size_t at = (it & (SLOTS - 1)) * set;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (tid + u * SOR_THREADS >= items) continue;
+      double* p = P + plane + own[u];
+      double v = *p;
+      if (!NEU || (open[1][u] & 1)) {
+        const double s = around(1, own[u], own2[1][u], open[1][u]);
+        v = relaxed(omega_black, v, s, rhs[1][u], open[1][u]);
+        if (test) acc += square(1, u, s, v);
+        *p = v;
+      }
+      const int yy = yz[u] & 0xffff, zz = yz[u] >> 16, i = own[u] - row_at(yy, zz);
+      unsigned long long m = (unsigned long long)__double_as_longlong(v);
+      if (m == EMPTY) m ^= 1;
+      auto put = [&](unsigned long long* to, int row) {
+        __hip_atomic_store(to + at + row * hx + i, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      };
+      const bool yl = yy == 0, yh = yy == ty - 1, zl = zz == 0, zh = zz == tz - 1;
+      if (yy < 2) put(mail_of(wyl, wz), 2 * tz + yy * tz + zz);
+      if (yy >= ty - 2) put(mail_of(wyh, wz), (ty - 1 - yy) * tz + zz);
+      if (zz < 2) put(mail_of(wy, wzl), 4 * tz + 2 * ty + zz * ty + yy);
+      if (zz >= tz - 2) put(mail_of(wy, wzh), 4 * tz + (tz - 1 - zz) * ty + yy);
+      const int corner = 4 * (ty + tz);
+      if (yl && zl) put(mail_of(wyl, wzl), corner + 3);
+      if (yh && zl) put(mail_of(wyh, wzl), corner + 2);
+      if (yl && zh) put(mail_of(wyl, wzh), corner + 1);
+      if (yh && zh) put(mail_of(wyh, wzh), corner);
+    }
+    omega = chebyshev_next(rj, omega_black);
+    omega_black = chebyshev_next(rj, omega);
   }
-  take(2 * n_it - 1);
+  take(n_it);
   __syncthreads();
   if (s_abort) return give_up();
-  if (tested(a, c.base + n_it)) {
+  if (test) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (tid + u * SOR_THREADS < items && (!NEU || (open[0][u] & 1)))
-        acc += square(0, u, around(0, u), P[own[u]]);
+        acc += square(0, u, around(0, own[u], own2[0][u], open[0][u]), P[own[u]]);
     sum_waves();
     __syncthreads();
     store_part(n_it);
@@ -415,7 +493,7 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
     const int r = t / a.nx, x = t - r * a.nx;
     const int zz = r / ty, yy = r - zz * ty, y = y0 + yy, z = z0 + zz;
     out[((long long)z * a.ny + y) * a.nx + x] =
-        P[((x + y + z) & 1) * plane + ((zz + 1) * ry + yy + 1) * hx + (x >> 1)];
+        P[((x + y + z) & 1) * plane + row_at(yy, zz) + (x >> 1)];
   }
   if (w == 0 && tid == 0) {
     SorControl* o = a.ctl + ((a.launch & 1) ^ 1);
@@ -440,7 +518,8 @@ __global__ __launch_bounds__(256) void k_mail_empty(unsigned long long* mail, si
 
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
-size_t tile_lds(int nx, int ty, int tz) { return (size_t)(ty + 2) * (tz + 2) * nx * 8; }
+size_t tile_lds(int nx, int ty, int tz) { return (size_t)(ty + 4) * (tz + 4) * nx * 8; }
+int box_rows(int ty, int tz) { return 4 * (ty + tz) + 4; }
 
 }  // namespace
 
@@ -449,14 +528,15 @@ size_t tile_lds(int nx, int ty, int tz) { return (size_t)(ty + 2) * (tz + 2) * n
 bool ek::sor_plan(int nx, int ny, int nz, SorPlan& p) {
   p = SorPlan{};
   const int hx = nx / 2;
-  for (int ty = 1; ty <= ny; ++ty) {
+  for (int ty = 2; ty <= ny; ++ty) {
     if (ny % ty) continue;
-    for (int tz = 1; tz <= nz; ++tz) {
+    for (int tz = 2; tz <= nz; ++tz) {
       if (nz % tz) continue;
       const int groups = (ny / ty) * (nz / tz);
-      const long long items = (long long)ty * tz * hx, face = 2LL * (ty + tz) * hx;
+      const long long items = std::max((long long)ty * tz, 2LL * (ty + tz)) * hx;
       if (groups > SOR_MAX_GROUPS || items > (long long)SOR_MAX_ITEMS * SOR_THREADS ||
-          face > (long long)SOR_MAX_TAKE * SOR_THREADS || tile_lds(nx, ty, tz) > SOR_LDS_MAX)
+          (long long)box_rows(ty, tz) * hx > (long long)SOR_MAX_TAKE * SOR_THREADS ||
+          tile_lds(nx, ty, tz) > SOR_LDS_MAX)
         continue;
       const int best = p.gy * p.gz;
       if (groups > best || (groups == best && ty + tz < p.ty + p.tz)) {
@@ -473,15 +553,15 @@ bool ek::sor_plan(int nx, int ny, int nz, SorPlan& p) {
 size_t ek::sor_bytes(int nx, int ny, int nz) {
   SorPlan p;
   if (!sor_plan(nx, ny, nz, p)) return 0;
-  const size_t groups = (size_t)p.gy * p.gz, face = 2 * (size_t)(p.ty + p.tz) * (nx / 2);
-  return al256((size_t)nx * ny * nz * 8) + al256(SLOTS * groups * face * 8) +
+  const size_t groups = (size_t)p.gy * p.gz, box = (size_t)box_rows(p.ty, p.tz) * (nx / 2);
+  return al256((size_t)nx * ny * nz * 8) + al256(SLOTS * groups * box * 8) +
          al256((size_t)2 * SOR_MAX_BATCH * groups * 8) + 256;
 }
 
 void ek_ctx::sor_setup(char* mem) {
   if (!sor_plan(p.nx, p.ny, p.nz, sor)) return;
   const size_t groups = (size_t)sor.gy * sor.gz;
-  const size_t slots = SLOTS * groups * 2 * (size_t)(sor.ty + sor.tz) * (p.nx / 2);
+  const size_t slots = SLOTS * groups * (size_t)box_rows(sor.ty, sor.tz) * (p.nx / 2);
   sor.tmp = (double*)mem;
   mem += al256((size_t)dims.n * 8);
   sor.mail = (unsigned long long*)mem;
@@ -519,7 +599,8 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
   a.every = p.poisson_check_every;
   a.rj = jacobi_radius();
   a.tol = p.poisson_tol;
-  const int groups = sor.gy * sor.gz, items = sor.ty * sor.tz * (p.nx / 2);
+  const int groups = sor.gy * sor.gz;
+  const int items = std::max(sor.ty * sor.tz, 2 * (sor.ty + sor.tz)) * (p.nx / 2);
   const size_t lds = tile_lds(p.nx, sor.ty, sor.tz);
   auto launch = [&](auto kernel) -> bool {
     if (lds > 64 * 1024 &&
@@ -536,7 +617,8 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
     }
     return true;
   };
-  const int u = (items + SOR_THREADS - 1) / SOR_THREADS;
+  int u = (items + SOR_THREADS - 1) / SOR_THREADS;
+  if (box_rows(sor.ty, sor.tz) * (p.nx / 2) > sor_take(1) * SOR_THREADS) u = std::max(u, 2);
   auto run = [&]() -> bool {
     if (insulating())
       return u == 1 ? launch(k_sor_team<true, 1>) : u == 2 ? launch(k_sor_team<true, 2>)
