@@ -395,7 +395,8 @@ ek_status ek_get_timing(struct ek_ctx* ctx, ek_timing* out);
  *   solve's psi buffer changes.  Without it the same kernels are launched one
  *   by one, in the same order, with bit-identical results.  When recording
  *   fails the context keeps to single launches.
- * EK_LAUNCH_OVERLAP: with a polymer, the fused lattice kernel updates every
+ * EK_LAUNCH_OVERLAP: with a polymer, in boxes whose lattice update is long
+ *   enough to pay for it (some 400,000 sites), the fused lattice kernel updates every
  *   site outside the beads' 4x4x4 boxes (the only nodes the friction
  *   reaches) on a second stream of the library's while the chain kernel runs
  *   on the context's stream; the box sites follow in a small launch once

@@ -330,6 +330,8 @@ void ek_ctx::record(int t, int k) {
   if (timing) (void)hipEventRecord(events[6 * t + k], stream);
 }
 
+constexpr double OVERLAP_MIN_SITES = 4e5;   // float32 sites without fluctuations
+
 template <typename T>
 ek_status ek_ctx::step_impl(int n_steps) {
   const ek_status st = step_loop<T>(n_steps);
@@ -348,8 +350,17 @@ ek_status ek_ctx::step_loop(int n_steps) {
   const SiteGrid g = bx_sites ? site_grid(p.nx, p.ny, p.nz, bx_sites) : lattice_grid(p.nx, p.ny, p.nz);
   const int nb = g.nblocks();
   const LBParams lp = lb_params();
-  // lattice update beside the chain (box sites after it): see EK_LAUNCH_OVERLAP
-  const bool overlap = overlap_md && n_beads > 0 && p.nx >= 4 && p.ny >= 4 && p.nz >= 4;
+  // lattice update beside the chain (box sites after it): see EK_LAUNCH_OVERLAP.
+  // It saves the update's time beside a chain of any usual length and costs
+  // the second stream's events, the launch for the box sites and their flags,
+  // some 30 us: a step of 64^3 in float32 with 8 / 32 beads takes 195 / 223 us
+  // with it and 182 / 211 without, 64x64x96 202 / 232 and 200 / 230, 64x64x128
+  // 217 / 242 and 227 / 251.  A float64 site takes twice, one with
+  // fluctuations 1.8 times as long as those.  With the timers on, whose events
+  // part the phases anyway, the mode is taken as it is set.
+  const double update = double(dims.n) * (sizeof(T) / 4) * (p.fluctuations ? 1.8 : 1.0);
+  const bool overlap = overlap_md && n_beads > 0 && p.nx >= 4 && p.ny >= 4 && p.nz >= 4 &&
+                       (update >= OVERLAP_MIN_SITES || timing);
   const int nb_bulk = lb_step_blocks(g, p.nz);
   const int nb_lb = nb_bulk + (overlap ? lb_tail_blocks(n_beads) : 0);
 
