@@ -1071,16 +1071,21 @@ struct UNetCarve {
 
 void carve_all(UNet& u, UNetCarve& c, int nx, int ny, int nz, bool training) {
   const size_t n0 = (size_t)nx * ny * nz, n1 = n0 / 8, n2 = n0 / 64;
-  if (training) u.x0 = c.take<uint32_t>(n0);
+  // x0, c1 and c2 are written in training only, but have their place in either
+  // layout: the workspace holds every layer's activations
+  uint32_t* x0 = c.take<uint32_t>(n0);
+  u.x0 = training ? x0 : nullptr;
   u.a1 = c.take<uint16_t>(n0 * 16);
   u.p1 = c.take<uint16_t>(n1 * 16);
   u.a2 = c.take<uint16_t>(n1 * 32);
   u.p2 = c.take<uint16_t>(n2 * 32);
   u.a3 = c.take<uint16_t>(n2 * 64);
   u.u3 = c.take<uint16_t>(n2 * 32);
-  if (training) u.c2 = c.take<uint16_t>(n1 * 32);
+  uint16_t* c2 = c.take<uint16_t>(n1 * 32);
+  u.c2 = training ? c2 : nullptr;
   u.u2 = c.take<uint16_t>(n1 * 16);
-  if (training) u.c1 = c.take<uint16_t>(n0 * 16);
+  uint16_t* c1 = c.take<uint16_t>(n0 * 16);
+  u.c1 = training ? c1 : nullptr;
   u.out = c.take<float>(n0);
   u.params = c.take<float>(UNET_PARAMS);
   u.wf = c.take<uint16_t>(UNET_PACKED);
