@@ -11,11 +11,11 @@ updates per second summed over the three species (MLUPS per species-step).
 
 The default workload is the large pore: 256 x 256 x 512 sites, a slab 20
 sites thick pierced by a pore of radius 10, salt 0.005, E_z = 0.02 and one
-chain of 256 beads (float32 populations, 15.3 GB of them, multigrid to a
+chain of 256 beads (float32 populations, 15.3 GB of them, the direct solve to a
 relative residual of 1e-8 in float64).  Unless --no-extra is given the same
 line also carries the 64 x 64 x 128 single pore with its 32-bead chain
 (`single_pore_64x64x128`, with the learned-warm-start comparison) and the
-64-replica ensemble of 48 x 48 x 96 pores in one persistent launch
+64-replica ensemble of 48 x 48 x 96 pores
 (`ensemble_64x48x48x96`), each measured the same way.
 
 The JSON line also carries:
@@ -185,7 +185,7 @@ def learned_comparison():
     sim = learned.simulate(params, scale, steps=100, warmup=10, log=lambda s: None)
     progress(f"learned start in the time loop: {json.dumps(sim)}")
     r = lambda x: round(x, 4)
-    out = {"tolerance": 1e-8, "finisher": "red-black multigrid (V(4,2) on the finest level)",
+    out = {"tolerance": 1e-8, "finisher": "red-black multigrid (V(4,2), level 1 solved directly)",
            "model": f"{info['n_traj'] * info['per_traj']} pairs, {info['epochs']} epochs"}
     for k, v in summary.items():
         out[k] = {"solves": v["n"], "cycles": r(v["cycles"]), "ms": r(v["ms"]),
@@ -288,9 +288,9 @@ def measure_context(wl, args, steps, warmup):
 
 
 def measure_ensemble(args, steps):
-    """64 uneven replicas of the 48 x 48 x 96 pore system in one persistent
-    launch per call; the autotuner picks the workgroup size and the number of
-    workgroups per replica during warm-up."""
+    """64 uneven replicas of the 48 x 48 x 96 pore system, each launch of a step
+    over all of them; the autotuner (which picks the shape of the persistent
+    launch that boxes without a direct solver take) serves as warm-up."""
     import numpy as np
     import torch
     from paper_1710_09421_amd import ek, workloads
@@ -298,7 +298,7 @@ def measure_ensemble(args, steps):
     wls = [workloads.ensemble_replica(r) for r in range(n_rep)]
     progress(f"{n_rep} replicas of {wls[0].shape[::-1]}, chains "
              f"{sorted(set(int(w.beads_R.shape[0]) for w in wls))}")
-    # the persistent kernel extrapolates linearly (it has no quadratic start)
+    # the ensemble extrapolates linearly (it has no quadratic start)
     start = ek.EK_WS_PREV if args.start == "previous" else ek.EK_WS_EXTRAP
     start_name = "previous" if args.start == "previous" else "extrapolated"
     ens = ek.ensemble_from_workloads(wls, precision=ek.EK_FP32, poisson_tol=1e-8,
@@ -315,7 +315,7 @@ def measure_ensemble(args, steps):
     dt = time.perf_counter() - t0
     progress(f"timed {steps} steps in {dt:.3f} s")
     ph1 = [ens.phase_times(r) for r in range(n_rep)]
-    # per-step phase times of each replica's team (the kernel's own clock)
+    # per-step phase times (the device's clock at the end of each phase)
     phase = {k: [(ph1[r][k] - ph0[r][k]) / steps for r in range(n_rep)]
              for k in ("charge", "poisson", "chain", "lb")}
     sites = n_rep * wls[0].sites
@@ -327,8 +327,7 @@ def measure_ensemble(args, steps):
     torch.cuda.synchronize()
     fluid = sum(w.fluid_sites for w in wls)
     lb_bytes = fluid * (2 * 57 * 4 + 8) + sites * 4
-    # the teams run their collide-and-stream phases side by side: the
-    # ensemble's lattice bytes of a step over the slowest team's phase time
+    # the ensemble's lattice bytes of a step over the longest phase time
     lb_max = max(phase["lb"])
     lb_gbs = lb_bytes / (lb_max * 1e-3) / 1e9
     return {
@@ -337,7 +336,7 @@ def measure_ensemble(args, steps):
         "dtype": "f32",
         "config": {
             "workload": f"ensemble of {n_rep} pore replicas 48x48x96 (E_z ~ U[0.01, 0.1], "
-                        f"chains of 16-64 beads), one persistent launch per call",
+                        f"chains of 16-64 beads), launches over all replicas",
             "sites": sites,
             "threads_per_workgroup": tune["threads"],
             "workgroups_per_replica": tune["group"],
@@ -348,7 +347,7 @@ def measure_ensemble(args, steps):
             "phase_ms_per_step_max": {k: round(float(np.max(v)), 4) for k, v in phase.items()},
         },
         "lb_phase_roofline": {
-            "phase": "fused collide-and-stream of all replicas (per-team clock in the kernel)",
+            "phase": "fused collide-and-stream of all replicas (device clock, with its sums)",
             "bound": "hbm", "achieved": round(lb_gbs, 1), "peak": 8000.0, "unit": "GB/s",
             "frac": round(lb_gbs / 8000.0, 4), "bytes_per_step": int(lb_bytes),
             "ms_per_step": round(lb_max, 4),

@@ -5,6 +5,7 @@
 //
 // Per lattice step:
 //   k_table_clear   drop last step's node table entries and their site flags
+//                   (k_chain_clear: and its box flags)
 //   k_deposit       bead charges q_i W(r - R_i) onto the 8 corner nodes
 //   (charge pass, Poisson solve)
 //   k_bead_box      per bead, the fields of time t on the 4x4x4 nodes around
