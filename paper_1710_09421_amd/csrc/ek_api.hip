@@ -648,7 +648,7 @@ void ek_destroy(ek_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->stream);
   if (ctx->side_stream) {
     (void)hipStreamSynchronize(ctx->side_stream);
-    (void)hipStreamDestroy(ctx->side_stream);
+    side_stream_give(ctx->side_device);
   }
   if (ctx->side_fork) (void)hipEventDestroy(ctx->side_fork);
   if (ctx->side_join) (void)hipEventDestroy(ctx->side_join);

@@ -12,6 +12,9 @@
 namespace ek {
 constexpr int MAX_BEADS = 1024;        // one workgroup advances a whole chain
 size_t bead_state_bytes(int max_beads);
+// The current device's side stream (null: cannot be made), to be given back.
+hipStream_t side_stream_take(int& device);
+void side_stream_give(int device);
 void launch_table_init(int* keys, long long* vals, hipStream_t s);
 void launch_table_init_bits(int* keys, long long* vals, int bits, hipStream_t s);
 size_t mg_workspace_bytes(int nx, int ny, int nz);
@@ -141,7 +144,8 @@ struct ek_ctx {
   bool overlap_md = true;              // lattice update outside the bead boxes beside the chain
   // second stream for the lattice update outside the bead boxes, beside the
   // chain kernel, and its fork / join events (created on first use)
-  hipStream_t side_stream = nullptr;
+  hipStream_t side_stream = nullptr;   // of the device, shared (side_stream_take)
+  int side_device = 0;
   hipEvent_t side_fork = nullptr, side_join = nullptr;
   // 6 per step: charge, poisson, md, lb start, lb end, chain end
   std::vector<hipEvent_t> events;
