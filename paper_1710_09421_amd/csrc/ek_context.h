@@ -28,7 +28,8 @@ struct SorPlan {
   bool ok = false;
   int ty = 0, tz = 0, gy = 0, gz = 0;   // rows of a tile along y and z; tiles
   double* tmp = nullptr;
-  unsigned long long* mail = nullptr;
+  uint64_t* mail = nullptr;
+  int bank = 0;                         // of the mailboxes, for the next launch (sor_mail.h)
   double* part = nullptr;
   SorControl* ctl = nullptr;
 };

@@ -11,22 +11,14 @@
 // iteration: a workgroup also relaxes the red sites of the ring around its
 // tile, for which it needs the black values of two rings, and after the black
 // half sweep it takes those from its eight neighbours.  (Sending each colour's
-// ring after its half sweep relaxes nothing twice but makes two trips: 3.1
-// instead of 1.95 us an iteration at 32^3, 3.6 instead of 2.25 at 64^3, 3.9
-// instead of 2.9 at 64x64x128.)  A solve of 64x64x128 to 1e-8 from zero takes
-// 1.4 ms (6.9 by single launches), a step of the 48x48x64 insulating pore 2.2
-// (16.6), a step of the 32^3 box to 1e-10 0.56 (1.76).
+// ring after its half sweep relaxes nothing twice but makes two trips, some 1.1
+// us more an iteration.)  An iteration takes 2.0 us at 32^3, 2.4 at 64^3, 3.0 at
+// 64x64x128; a solve of 64x64x128 to 1e-8 from zero 1.42 ms (6.9 by single
+// launches), two steps of the 48x48x64 insulating pore with their read-out 4.1
+// to 4.8 (33), of the 32^3 box to 1e-10 1.18 (3.5).
 //
-// Exchange: every value travels as one 64-bit device-scope store into a slot
-// of the receiver's mailbox; the receiver polls the slot itself until it no
-// longer holds EMPTY (a NaN no arithmetic produces), then empties it again.
-// No flag follows the data and no fence is needed: a slot is one word, and
-// nothing else is read because of it.  Iteration g uses slot set g & 3.  A set
-// is written again four iterations later, by when its reader has emptied it:
-// the reader's polling wait of iteration g + 2 also waits for the stores that
-// emptied set g, and the sender cannot send in iteration g + 4 before it has
-// received what the reader sent after that.  All values sent are taken before
-// a launch ends, so the mailboxes are empty between launches.
+// Exchange: every value travels as one 64-bit device-scope store into a slot of
+// the receiver's mailbox, which the receiver polls (sor_mail.h).
 //
 // The launch is cooperative, so every workgroup it waits for is resident; a
 // wait is bounded all the same (the solve then fails, and the context takes
@@ -46,24 +38,23 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 
 #include "ek_context.h"
 #include "reduce.h"
+#include "sor_mail.h"
 
 using namespace ek;
 
 namespace {
 
-constexpr unsigned long long EMPTY = 0xFFF7A5C35A3C7F11ull;
-constexpr int SLOTS = 4;
 constexpr int SOR_THREADS = 512;
 constexpr int SOR_WAVES = SOR_THREADS / 64;
 constexpr int SOR_MAX_BATCH = 256;
 constexpr int SOR_NEAR = 12;          // iterations left within which a batch crosses the end
 constexpr int SOR_SHORT = 4;          // else it stops this many before the expected end
 constexpr int SOR_MAX_ITEMS = 4;      // sites of a colour per thread
-constexpr int sor_take(int u) { return u == 1 ? 4 : 8; }   // values a thread takes per iteration
-constexpr int SOR_MAX_TAKE = sor_take(SOR_MAX_ITEMS);
+constexpr int SOR_MAX_TAKE = 8;       // values a thread takes per iteration
 constexpr int SOR_MAX_GROUPS = 256;   // one workgroup per compute unit
 constexpr size_t SOR_LDS_MAX = 150 * 1024;
 constexpr int SOR_SPIN_LIMIT = 1 << 20;
@@ -92,7 +83,8 @@ struct SorArgs {
   const uint32_t* mask;
   const PoissonScalars* ps;
   SorControl* ctl;    // [2]: read at launch & 1, written at the other
-  unsigned long long* mail;
+  uint64_t* mail;     // [bank][set][workgroup][row][x / 2]
+  int bank;           // of this launch
   double* part;       // [2][iteration of the batch][workgroup]: likewise
   int launch;
   int first;          // length of the first batch
@@ -190,14 +182,23 @@ __device__ inline SorControl sor_verdict(const SorArgs& a, double* rel) {
 
 // NEU: insulating walls (fluid sites only, the link words' bits 1..6 mark the
 // solid face neighbours, see kernels_poisson.hip).  U: sites of a colour per
-// thread, of the tile and of its ring.  Colour 0 is red here, colour 1 black.
-template <bool NEU, int U>
+// thread, of the tile and of its ring.  TAKE: values a thread takes after an
+// iteration.  Colour 0 is red here, colour 1 black.
+template <bool NEU, int U, int TAKE>
 __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
   extern __shared__ double P[];      // [colour][row of the tile and two rings][x / 2]
-  constexpr int TAKE = sor_take(U);
   __shared__ int s_abort;
   __shared__ double s_rel[SOR_MAX_BATCH];
   __shared__ double s_sum[SOR_WAVES];
+  {
+    // the next launch's bank of this workgroup's slots
+    const int box = (4 * (a.ty + a.tz) + 4) * (a.nx / 2);
+    for (int t = threadIdx.x; t < SOR_SETS * box; t += SOR_THREADS) {
+      const int half = t >= box;
+      uint64_t* to = a.mail + ((size_t)((a.bank ^ 1) * SOR_SETS + half) * gridDim.x + blockIdx.x) * box;
+      __hip_atomic_store(to + t - half * box, SOR_UNSENT, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
   const SorControl c = sor_verdict(a, s_rel);
   if (c.state >= SOR_FINAL) {
     if (blockIdx.x == 0 && threadIdx.x == 0) a.ctl[(a.launch & 1) ^ 1] = c;
@@ -296,13 +297,13 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
   // its mailbox: 2 tz rows below and above in y (yy = -1 - d and ty + d at
   // d tz + zz), 2 ty rows below and above in z, four corner rows.
   const int box_rows = 4 * (ty + tz) + 4, box = box_rows * hx;
-  const size_t set = (size_t)W * box;
-  int dst[TAKE];             // LDS index, or -1
+  // (a thread with fewer than TAKE values takes its first one again, or none in
+  // place of the last)
+  int from[TAKE], dst[TAKE]; // value of the mailbox, LDS index
 #pragma unroll
   for (int v = 0; v < TAKE; ++v) {
-    const int t = tid + v * SOR_THREADS;
-    dst[v] = -1;
-    if (t >= box) continue;
+    const int own_value = tid + v * SOR_THREADS, t = own_value < box ? own_value : min(tid, box - 1);
+    from[v] = t;
     int k = t / hx, yy, zz;
     const int i = t - k * hx;
     if (k < 2 * tz) {
@@ -327,40 +328,54 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
   // the mailboxes of the eight neighbours
   const int wyl = wy == 0 ? a.gy - 1 : wy - 1, wyh = wy == a.gy - 1 ? 0 : wy + 1;
   const int wzl = wz == 0 ? a.gz - 1 : wz - 1, wzh = wz == a.gz - 1 ? 0 : wz + 1;
-  auto mail_of = [&](int y, int z) { return a.mail + (size_t)(z * a.gy + y) * box; };
-  unsigned long long* const mine = mail_of(wy, wz);
+  const size_t set = (size_t)W * box;
+  uint64_t* const mail = a.mail + a.bank * SOR_SETS * set;
+  auto mail_of = [&](int y, int z) { return mail + (size_t)(z * a.gy + y) * box; };
+  const uint64_t* const mine = mail_of(wy, wz);
+  constexpr int LAST = TAKE - 1;
+  const bool has_last = tid + LAST * SOR_THREADS < box;
+  // the words of the last two iterations: received, and sent (the same to all)
+  uint64_t got[2][TAKE], gave[2][U];
+#pragma unroll
+  for (int k = 0; k < TAKE; ++k) got[0][k] = got[1][k] = SOR_UNSENT;
+#pragma unroll
+  for (int u = 0; u < U; ++u) gave[0][u] = gave[1][u] = SOR_UNSENT;
   // takes the values sent after iteration it into the rings
   auto take = [&](int it) {
-    unsigned long long* from = mine + (it & (SLOTS - 1)) * set + tid;
-    unsigned long long v[TAKE];
+    const uint64_t* words = mine + (it & 1) * set;
+    uint64_t v[TAKE];
     int spins = 0;
-    bool all;
+    bool waits;
     // The values cannot be there before a trip through the memory side; a
     // look before that comes back empty only after the next could have come
-    // back full (64^3: 2.7 us an iteration without the pause of 512 clocks,
-    // 2.25 with it, 2.4 and 2.6 with twice and three times as long a one).
-    __builtin_amdgcn_s_sleep(8);
+    // back full (64x48x48: 2.55 us an iteration after a pause of 256 clocks,
+    // 2.43 of 512, 2.23 of 768, 2.29 of 1024; 64x64x128: 3.09, 3.02, 3.03, 3.11).
+    __builtin_amdgcn_s_sleep(12);
+    if (tid >= box) return;
     do {
-      all = true;
+      // a branch for the last value only: each would wait for the load before
+      // it (a branch per value: 2.45 instead of 2.00 us at 32^3)
 #pragma unroll
-      for (int k = 0; k < TAKE; ++k) v[k] = 0;
+      for (int k = 0; k < LAST; ++k)
+        v[k] = __hip_atomic_load(words + from[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      v[LAST] = ~got[0][LAST];
+      if (has_last)
+        v[LAST] = __hip_atomic_load(words + from[LAST], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      waits = false;
 #pragma unroll
-      for (int k = 0; k < TAKE; ++k)
-        if (dst[k] >= 0)
-          v[k] = __hip_atomic_load(from + k * SOR_THREADS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int k = 0; k < TAKE; ++k) all = all && v[k] != EMPTY;
-      if (!all && ++spins > SOR_SPIN_LIMIT) {
+      for (int k = 0; k < TAKE; ++k) waits |= v[k] == got[0][k];
+      if (waits && ++spins > SOR_SPIN_LIMIT) {
         s_abort = 1;
         break;
       }
-    } while (!all);
+    } while (waits);
 #pragma unroll
-    for (int k = 0; k < TAKE; ++k)
-      if (dst[k] >= 0) {
-        P[plane + dst[k]] = __longlong_as_double((long long)v[k]);
-        __hip_atomic_store(from + k * SOR_THREADS, EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
+    for (int k = 0; k < TAKE; ++k) {
+      if (k < LAST || has_last)
+        P[plane + dst[k]] = __longlong_as_double((long long)sor_value(v[k], got[0][k]));
+      got[0][k] = got[1][k];
+      got[1][k] = v[k];
+    }
   };
   const double rj = a.rj;
   // this iteration's factors of red and black; the next ones are computed
@@ -445,7 +460,7 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
     __syncthreads();
     if (prev) store_part(it - 1);
     // black, and to the neighbours
-    const size_t at = (it & (SLOTS - 1)) * set;
+    const size_t at = (it & 1) * set;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (tid + u * SOR_THREADS >= items) continue;
@@ -458,9 +473,10 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
         *p = v;
       }
       const int yy = yz[u] & 0xffff, zz = yz[u] >> 16, i = own[u] - row_at(yy, zz);
-      unsigned long long m = (unsigned long long)__double_as_longlong(v);
-      if (m == EMPTY) m ^= 1;
-      auto put = [&](unsigned long long* to, int row) {
+      const uint64_t m = sor_word((uint64_t)__double_as_longlong(v), gave[0][u]);
+      gave[0][u] = gave[1][u];
+      gave[1][u] = m;
+      auto put = [&](uint64_t* to, int row) {
         __hip_atomic_store(to + at + row * hx + i, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       };
       const bool yl = yy == 0, yh = yy == ty - 1, zl = zz == 0, zh = zz == tz - 1;
@@ -511,15 +527,18 @@ __global__ void k_sor_reset(SorControl* c) {
   if (threadIdx.x < 2) c[threadIdx.x] = SorControl{SOR_START, 0, 0, 0, 0, 0, 1.0, 1.0};
 }
 
-__global__ __launch_bounds__(256) void k_mail_empty(unsigned long long* mail, size_t n) {
+__global__ __launch_bounds__(256) void k_mail_fill(uint64_t* mail, size_t n) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) mail[i] = EMPTY;
+  if (i < n) mail[i] = SOR_UNSENT;
 }
 
 size_t al256(size_t b) { return (b + 255) & ~size_t(255); }
 
 size_t tile_lds(int nx, int ty, int tz) { return (size_t)(ty + 4) * (tz + 4) * nx * 8; }
 int box_rows(int ty, int tz) { return 4 * (ty + tz) + 4; }
+size_t mail_words(const SorPlan& p, int nx) {
+  return (size_t)SOR_BANKS * SOR_SETS * p.gy * p.gz * box_rows(p.ty, p.tz) * (nx / 2);
+}
 
 }  // namespace
 
@@ -553,24 +572,24 @@ bool ek::sor_plan(int nx, int ny, int nz, SorPlan& p) {
 size_t ek::sor_bytes(int nx, int ny, int nz) {
   SorPlan p;
   if (!sor_plan(nx, ny, nz, p)) return 0;
-  const size_t groups = (size_t)p.gy * p.gz, box = (size_t)box_rows(p.ty, p.tz) * (nx / 2);
-  return al256((size_t)nx * ny * nz * 8) + al256(SLOTS * groups * box * 8) +
+  const size_t groups = (size_t)p.gy * p.gz;
+  return al256((size_t)nx * ny * nz * 8) + al256(mail_words(p, nx) * 8) +
          al256((size_t)2 * SOR_MAX_BATCH * groups * 8) + 256;
 }
 
 void ek_ctx::sor_setup(char* mem) {
   if (!sor_plan(p.nx, p.ny, p.nz, sor)) return;
   const size_t groups = (size_t)sor.gy * sor.gz;
-  const size_t slots = SLOTS * groups * (size_t)box_rows(sor.ty, sor.tz) * (p.nx / 2);
   sor.tmp = (double*)mem;
   mem += al256((size_t)dims.n * 8);
-  sor.mail = (unsigned long long*)mem;
-  mem += al256(slots * 8);
+  sor.mail = (uint64_t*)mem;
+  mem += al256(mail_words(sor, p.nx) * 8);
   sor.part = (double*)mem;
   mem += al256((size_t)2 * SOR_MAX_BATCH * groups * 8);
   sor.ctl = (SorControl*)mem;
-  hipLaunchKernelGGL(k_mail_empty, dim3(int((slots + 255) / 256)), dim3(256), 0, stream, sor.mail,
-                     slots);
+  const size_t words = mail_words(sor, p.nx);
+  hipLaunchKernelGGL(k_mail_fill, dim3(int((words + 255) / 256)), dim3(256), 0, stream, sor.mail,
+                     words);
   sor.ok = true;
 }
 
@@ -609,23 +628,31 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
       (void)hipGetLastError();
       return false;
     }
+    a.bank = sor.bank;
     void* args[] = {(void*)&a};
     if (hipLaunchCooperativeKernel((const void*)kernel, dim3(groups), dim3(SOR_THREADS), args,
                                    (unsigned)lds, stream) != hipSuccess) {
       (void)hipGetLastError();
       return false;
     }
+    sor.bank ^= 1;
     return true;
   };
-  int u = (items + SOR_THREADS - 1) / SOR_THREADS;
-  if (box_rows(sor.ty, sor.tz) * (p.nx / 2) > sor_take(1) * SOR_THREADS) u = std::max(u, 2);
-  auto run = [&]() -> bool {
-    if (insulating())
-      return u == 1 ? launch(k_sor_team<true, 1>) : u == 2 ? launch(k_sor_team<true, 2>)
-                                                           : launch(k_sor_team<true, 4>);
-    return u == 1 ? launch(k_sor_team<false, 1>) : u == 2 ? launch(k_sor_team<false, 2>)
-                                                          : launch(k_sor_team<false, 4>);
+  const int u = (items + SOR_THREADS - 1) / SOR_THREADS;
+  const int take = (box_rows(sor.ty, sor.tz) * (p.nx / 2) + SOR_THREADS - 1) / SOR_THREADS;
+  // the smallest instance (the ring has two sites a row and the mailbox four
+  // values, and a corner's rows: take <= 2 u + 1 up to 64 sites along x)
+  auto run_as = [&](auto neu) -> bool {
+    constexpr bool NEU = decltype(neu)::value;
+    if (u == 1 && take == 1) return launch(k_sor_team<NEU, 1, 1>);
+    if (u == 1 && take == 2) return launch(k_sor_team<NEU, 1, 2>);
+    if (u == 1 && take == 3) return launch(k_sor_team<NEU, 1, 3>);
+    if (u == 1 && take <= 4) return launch(k_sor_team<NEU, 1, 4>);
+    if (u <= 2 && take <= 4) return launch(k_sor_team<NEU, 2, 4>);
+    if (u <= 2) return launch(k_sor_team<NEU, 2, 8>);
+    return launch(k_sor_team<NEU, 4, 8>);
   };
+  auto run = [&] { return insulating() ? run_as(std::true_type{}) : run_as(std::false_type{}); };
   hipLaunchKernelGGL(k_sor_reset, dim3(1), dim3(64), 0, stream, sor.ctl);
   SorControl c{};
   // full batches, the two that end the solve, its second run and the verdict
@@ -653,7 +680,7 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
     std::memcpy(&c, pinned, sizeof c);
   }
   if (c.aborted) {
-    sor.ok = false;   // the mailboxes are no longer empty: single launches from now on
+    sor.ok = false;   // single launches from now on
     st = fail(EK_EHIP, "a workgroup of the SOR iterations waited beyond its limit");
     return true;
   }
