@@ -24,6 +24,7 @@ size_t mg_direct_bytes(int nx, int ny, int nz);   // level 1's direct solver (0:
 // Tiles of the SOR that runs batches of iterations in one launch
 // (kernels_sor.hip), and its memory.
 struct SorControl;
+constexpr int SOR_SPIN_LIMIT = 1 << 20;   // looks of a wait (about a second)
 struct SorPlan {
   bool ok = false;
   int ty = 0, tz = 0, gy = 0, gz = 0;   // rows of a tile along y and z; tiles
@@ -32,6 +33,9 @@ struct SorPlan {
   int bank = 0;                         // of the mailboxes, for the next launch (sor_mail.h)
   double* part = nullptr;
   SorControl* ctl = nullptr;
+  // for the tests (ek_test_sor_batches): the limit of the waits from one launch
+  // of a solve on, and a launch that is refused
+  int spin_limit = SOR_SPIN_LIMIT, limit_from = 0, refuse_at = -1;
 };
 bool sor_plan(int nx, int ny, int nz, SorPlan& p);
 size_t sor_bytes(int nx, int ny, int nz);

@@ -20,9 +20,12 @@
 // Exchange: every value travels as one 64-bit device-scope store into a slot of
 // the receiver's mailbox, which the receiver polls (sor_mail.h).
 //
-// The launch is cooperative, so every workgroup it waits for is resident; a
-// wait is bounded all the same (the solve then fails, and the context takes
-// the single launches from then on).
+// The launch is cooperative, so the device has room for all its workgroups at
+// once; kernels of other queues may still keep some of them from starting for a
+// while, and a wait is bounded.  When one gives up, or a launch is refused, the
+// solve goes on with single launches from the iterate that the last batch
+// started from (its input is whole whatever became of its result), with the same
+// bits, and the context takes single launches from then on.
 //
 // Convergence: every tested iteration's sum of squared residuals costs no
 // reads of its own (at a colour-1 site from its update's neighbours and the
@@ -57,7 +60,6 @@ constexpr int SOR_MAX_ITEMS = 4;      // sites of a colour per thread
 constexpr int SOR_MAX_TAKE = 8;       // values a thread takes per iteration
 constexpr int SOR_MAX_GROUPS = 256;   // one workgroup per compute unit
 constexpr size_t SOR_LDS_MAX = 150 * 1024;
-constexpr int SOR_SPIN_LIMIT = 1 << 20;
 
 enum : int { SOR_START = 0, SOR_RAN = 1, SOR_REPLAYED = 2, SOR_FINAL = 3, SOR_LIMIT = 4 };
 
@@ -70,7 +72,7 @@ struct ek::SorControl {
                       // scratch one), its result is in the other; FINAL, LIMIT: the result
   int base, n;        // iterations before it, and of it
   int found;          // iteration that met the tolerance
-  int aborted;        // a wait ran into its limit
+  int aborted;        // a wait ran into its limit: cur and base hold, no result
   double omega;       // relaxation factor of its first half sweep
   double omega_next;  // ... of the half sweep after it
 };
@@ -85,6 +87,7 @@ struct SorArgs {
   SorControl* ctl;    // [2]: read at launch & 1, written at the other
   uint64_t* mail;     // [bank][set][workgroup][row][x / 2]
   int bank;           // of this launch
+  int spin_limit;     // looks in vain after which a wait gives up
   double* part;       // [2][iteration of the batch][workgroup]: likewise
   int launch;
   int first;          // length of the first batch
@@ -364,7 +367,7 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
       waits = false;
 #pragma unroll
       for (int k = 0; k < TAKE; ++k) waits |= v[k] == got[0][k];
-      if (waits && ++spins > SOR_SPIN_LIMIT) {
+      if (waits && ++spins > a.spin_limit) {
         s_abort = 1;
         break;
       }
@@ -429,9 +432,12 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
     }
   };
   auto give_up = [&] {
-    if (tid == 0)
-      for (int k = 0; k < 2; ++k)
-        __hip_atomic_store(&a.ctl[k].aborted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid != 0) return;
+    // the same values from every workgroup that gives up, or ends (w == 0)
+    SorControl* o = a.ctl + ((a.launch & 1) ^ 1);
+    __hip_atomic_store(&o->cur, c.cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&o->base, c.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&o->aborted, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   bool test = false;
   int since = c.base % a.every;          // iterations since the last multiple of `every`
@@ -514,8 +520,8 @@ __global__ __launch_bounds__(SOR_THREADS) void k_sor_team(SorArgs a) {
   if (w == 0 && tid == 0) {
     SorControl* o = a.ctl + ((a.launch & 1) ^ 1);
     o->state = c.state;
-    o->cur = c.cur;
-    o->base = c.base;
+    __hip_atomic_store(&o->cur, c.cur, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&o->base, c.base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     o->n = c.n;
     o->found = c.found;
     o->omega = c.omega;
@@ -593,8 +599,15 @@ void ek_ctx::sor_setup(char* mem) {
   sor.ok = true;
 }
 
+extern "C" void ek_test_sor_batches(ek_ctx* ctx, int spin_limit, int limit_from, int refuse_at) {
+  ctx->sor.spin_limit = spin_limit;
+  ctx->sor.limit_from = limit_from;
+  ctx->sor.refuse_at = refuse_at;
+}
+
 // The solve of sor_solve by batches in one launch each; false (and x as it
-// was) where that is not possible here.
+// was) where that is not possible here.  `it` iterations are in x afterwards;
+// the caller goes on from there where h says that the solve is not done.
 bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int& it, ek_status& st) {
   st = EK_OK;
   if (!sor.ok) return false;
@@ -628,6 +641,8 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
       (void)hipGetLastError();
       return false;
     }
+    if (a.launch == sor.refuse_at) return false;
+    a.spin_limit = a.launch >= sor.limit_from ? sor.spin_limit : SOR_SPIN_LIMIT;
     a.bank = sor.bank;
     void* args[] = {(void*)&a};
     if (hipLaunchCooperativeKernel((const void*)kernel, dim3(groups), dim3(SOR_THREADS), args,
@@ -661,14 +676,16 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
   a.first = std::min({expect > SOR_NEAR ? expect - SOR_SHORT : expect + 2, SOR_MAX_BATCH,
                       p.poisson_max_iter});
   int ahead = expect / SOR_MAX_BATCH + 4;
-  while (c.state < SOR_FINAL && !c.aborted) {
-    for (int k = 0; k < ahead; ++k, ++a.launch)
-      if (!run()) {
+  bool refused = false;
+  while (c.state < SOR_FINAL && !c.aborted && !refused) {
+    for (int k = 0; k < ahead && !refused; ++k) {
+      refused = !run();
+      if (refused && a.launch == 0) {
         sor.ok = false;
-        if (a.launch == 0) return false;
-        st = fail(EK_EHIP, "a cooperative launch of the SOR iterations was refused");
-        return true;
+        return false;
       }
+      if (!refused) ++a.launch;
+    }
     ahead = 2;
     if (hipMemcpyAsync(pinned, sor.ctl + (a.launch & 1), sizeof c, hipMemcpyDeviceToHost, stream) !=
         hipSuccess) {
@@ -679,14 +696,16 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
     if (st) return true;
     std::memcpy(&c, pinned, sizeof c);
   }
-  if (c.aborted) {
-    sor.ok = false;   // single launches from now on
-    st = fail(EK_EHIP, "a workgroup of the SOR iterations waited beyond its limit");
-    return true;
-  }
+  // without a result of its own: from what the last launch started from
+  const bool left = c.aborted || c.state < SOR_FINAL;
+  if (c.aborted || refused) sor.ok = false;
   if (c.cur == 1 &&
       hipMemcpyAsync(x, sor.tmp, dims.n * 8, hipMemcpyDeviceToDevice, stream) != hipSuccess) {
     st = fail(EK_EHIP, "copying the iterate failed");
+    return true;
+  }
+  if (left) {
+    it = c.base;
     return true;
   }
   // the residual of the result as the single launches take it
