@@ -744,6 +744,15 @@ ek_status ek_ensemble_create(const ek_params* base, int32_t n_rep, int32_t max_b
     }
   }
   ec.lds_bits = lds_bits_for(max_beads);
+  // the tables are copied without a stream: what is still to run on the
+  // workspace's memory in the ensemble's stream has to be over
+  if (hipStreamSynchronize(e->stream) != hipSuccess) {
+    (void)hipGetLastError();
+    if (own) (void)hipFree(ws);
+    delete e;
+    g_ens_error = "synchronising the stream failed";
+    return EK_EHIP;
+  }
   RepBatch& bt = e->batch;
   replicas_setup(bt, batch_mem, base->nx, base->ny, base->nz, n_rep);
   bt.reps = e->reps_dev;
