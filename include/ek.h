@@ -404,6 +404,9 @@ ek_status ek_get_timing(struct ek_ctx* ctx, ek_timing* out);
  *   site is updated by the same arithmetic either way (bit-identical fields
  *   and beads); only the order of the float64 mass and momentum sums
  *   differs.  Needs nx, ny, nz >= 4, else the kernels run one after the other.
+ *   The contexts of a device share the second stream: a step that uses it
+ *   first waits on the host for what the caller has enqueued on the context's
+ *   stream, so that this holds up no other context.
  * A context whose stream the caller is recording itself cannot run a step
  * (the step reads convergence flags back to the host). */
 enum { EK_LAUNCH_GRAPHS = 1, EK_LAUNCH_OVERLAP = 2 };

@@ -361,6 +361,12 @@ ek_status ek_ctx::step_loop(int n_steps) {
   const double update = double(dims.n) * (sizeof(T) / 4) * (p.fluctuations ? 1.8 : 1.0);
   const bool overlap = overlap_md && n_beads > 0 && p.nx >= 4 && p.ny >= 4 && p.nz >= 4 &&
                        (update >= OVERLAP_MIN_SITES || timing);
+  // The side stream is shared with other contexts: nothing may stand in it that
+  // waits for work of the caller's, which may in turn wait for one of those.
+  if (overlap) {
+    const ek_status st = sync();
+    if (st) return st;
+  }
   const int nb_bulk = lb_step_blocks(g, p.nz);
   const int nb_lb = nb_bulk + (overlap ? lb_tail_blocks(n_beads) : 0);
 

@@ -178,8 +178,9 @@ BeadTableView ek_ctx::bead_view() const {
 // queues (four per process) from the contexts' own streams: with four such
 // contexts alive a step of the 64x64x128 pore with fluctuations took 530 us
 // instead of 275.  Each use is ordered by its context's own events; that
-// another context's update may stand in between delays it but cannot block it,
-// since what a side update waits for never waits for another one.
+// another context's update may stand in between delays it but cannot block it:
+// what a side update waits for is work of the library's own, since a step
+// enqueues none before its stream has finished what the caller put there.
 // (Never destroyed: a context may be released while the process ends.)
 static std::mutex& side_mutex = *new std::mutex;
 static auto& side_streams = *new std::map<int, std::pair<hipStream_t, int>>;   // device -> stream, users
