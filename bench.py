@@ -289,8 +289,8 @@ def measure_context(wl, args, steps, warmup):
 
 def measure_ensemble(args, steps):
     """64 uneven replicas of the 48 x 48 x 96 pore system, each launch of a step
-    over all of them; the autotuner (which picks the shape of the persistent
-    launch that boxes without a direct solver take) serves as warm-up."""
+    over all of them; the autotuner serves as warm-up (it has a shape to choose
+    for the persistent launch only, that boxes without a direct solver take)."""
     import numpy as np
     import torch
     from paper_1710_09421_amd import ek, workloads
@@ -338,9 +338,7 @@ def measure_ensemble(args, steps):
             "workload": f"ensemble of {n_rep} pore replicas 48x48x96 (E_z ~ U[0.01, 0.1], "
                         f"chains of 16-64 beads), launches over all replicas",
             "sites": sites,
-            "threads_per_workgroup": tune["threads"],
-            "workgroups_per_replica": tune["group"],
-            "poisson": f"mg to 1e-8 per replica from the {start_name} start, "
+            "poisson": f"direct to 1e-8 per replica from the {start_name} start, "
                        f"last solve {min(cycles)}-{max(cycles)} cycles",
             "lb_bytes_per_step_gb": round(lb_bytes / 1e9, 3),
             "phase_ms_per_step": {k: round(float(np.mean(v)), 4) for k, v in phase.items()},

@@ -554,8 +554,8 @@ ek_status ek_ensemble_get_stats(ek_ensemble* ens, int32_t r, ek_stats* out);
  * NULL ms; EK_EHIP when the device reports no wall-clock rate. */
 ek_status ek_ensemble_phase_times(ek_ensemble* ens, int32_t r, double* ms);
 
-/* Workgroup size of the persistent kernel (256, 512 or 1024; launched steps
- * have shapes of their own). */
+/* Workgroup size of the persistent kernel (256, 512 or 1024; without effect on
+ * launched steps, which have shapes of their own). */
 ek_status ek_ensemble_set_threads(ek_ensemble* ens, int32_t threads);
 
 /* Workgroups per replica (1, 2 or 4).  With more than one, the replica's
@@ -565,14 +565,17 @@ ek_status ek_ensemble_set_threads(ek_ensemble* ens, int32_t threads);
  * the chain run in the team's first workgroup.  Sums are taken per
  * workgroup, then over the team in a fixed order, so results do not depend
  * on timing (but may differ in the last bits between team sizes).  A launch
- * the device cannot make co-resident is refused with EK_EHIP. */
+ * the device cannot make co-resident is refused with EK_EHIP.  Without effect on
+ * launched steps. */
 ek_status ek_ensemble_set_group(ek_ensemble* ens, int32_t group);
 
 /* Autotuner: times `steps` ensemble steps with every candidate workgroup size
  * and team size, in two interleaved passes over the candidates, each keeping
  * its faster pass (the replicas advance by 1 + 2 `steps` steps per candidate,
  * like a warm-up; team sizes the device refuses are skipped), and keeps the
- * fastest; *out (may be NULL) receives the choice and its time. */
+ * fastest; *out (may be NULL) receives the choice and its time.  Launched steps
+ * are the same with every candidate: they advance as much, and the workgroup
+ * and team size stay as they are. */
 ek_status ek_ensemble_autotune(ek_ensemble* ens, int32_t steps, ek_tune_result* out);
 
 #ifdef __cplusplus

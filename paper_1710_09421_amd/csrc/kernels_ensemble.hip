@@ -978,10 +978,13 @@ ek_status ek_ensemble_autotune(ek_ensemble* e, int32_t steps, ek_tune_result* ou
   if (st) return st;
   int best = e->threads, best_group = e->group;
   double best_ms = INFINITY;
+  // launched steps have shapes of their own: nothing to choose by these times
+  const bool choose = !launched_path(e);
   for (int i = 0; i < NT; ++i)
     for (int j = 0; j < NG; ++j)
       if (fits[i][j] && per_c[i][j] < best_ms) {
         best_ms = per_c[i][j];
+        if (!choose) continue;
         best = threads_c[i];
         best_group = groups_c[j];
       }

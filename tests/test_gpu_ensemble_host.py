@@ -1,4 +1,5 @@
-"""An ensemble whose workspace's memory still has work pending on its stream."""
+"""The ensemble's host side: a workspace whose memory still has work pending on
+the ensemble's stream, and the tuner where there is no launch shape to choose."""
 import numpy as np
 import pytest
 
@@ -55,3 +56,16 @@ def test_workspace_with_work_pending_on_the_stream(ek):
             del ens
             assert all(np.array_equal(a, b) for a, b in zip(got, want))
     ref.close()
+
+
+@pytest.mark.parametrize("threads,group", [(256, 1), (1024, 2), (512, 4)])
+def test_tuning_launched_steps_keeps_the_shape(ek, threads, group):
+    """Steps launched over all replicas are the same with every shape."""
+    ens = ensemble(ek, [replica((16, 16, 16), 9)], poisson_max_iter=200)
+    ens.set_threads(threads)
+    ens.set_group(group)
+    res = ens.autotune(steps=2)
+    assert (res["threads"], res["group"]) == (threads, group)
+    assert 0 < res["ms_per_step"] < 1e3
+    assert ens.stats(0)["step"] == 9 * (1 + 2 + 2)
+    ens.close()
