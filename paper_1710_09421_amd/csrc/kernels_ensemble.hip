@@ -633,8 +633,9 @@ ek_status run_steps(ek_ensemble* e, int n_steps, int threads, int group) {
     const RepDev& R = e->reps[r];
     char buf[200];
     if (R.status == ST_NOCONV) {
-      std::snprintf(buf, sizeof buf, "replica %d: multigrid did not reach %.3g in %d cycles (residual %.3e)",
-                    r, e->p.poisson_tol, R.last_cycles, R.last_res);
+      std::snprintf(buf, sizeof buf, "replica %d: %s did not reach %.3g in %d cycles (residual %.3e)", r,
+                    launched_path(e) ? "the direct solve" : "multigrid", e->p.poisson_tol, R.last_cycles,
+                    R.last_res);
       return e->fail(EK_ENOCONV, buf);
     }
     if (R.status == ST_UNSTABLE) {

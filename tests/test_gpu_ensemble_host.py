@@ -1,5 +1,6 @@
 """The ensemble's host side: a workspace whose memory still has work pending on
-the ensemble's stream, and the tuner where there is no launch shape to choose."""
+the ensemble's stream, the tuner where there is no launch shape to choose, and
+the solver that a message names."""
 import numpy as np
 import pytest
 
@@ -68,4 +69,14 @@ def test_tuning_launched_steps_keeps_the_shape(ek, threads, group):
     assert (res["threads"], res["group"]) == (threads, group)
     assert 0 < res["ms_per_step"] < 1e3
     assert ens.stats(0)["step"] == 9 * (1 + 2 + 2)
+    ens.close()
+
+
+@pytest.mark.parametrize("cycles,name", [(30, "the direct solve"), (19, "multigrid")])
+def test_no_convergence_names_the_solver(ek, cycles, name):
+    ens = ensemble(ek, [replica((16, 16, 16), 9)], poisson_max_iter=cycles, poisson_tol=1e-17)
+    with pytest.raises(ek.EKError) as e:
+        ens.step(1)
+    assert e.value.status == ek.EK_ENOCONV
+    assert f"replica 0: {name} did not reach 1e-17 in {cycles} cycles" in str(e.value)
     ens.close()
