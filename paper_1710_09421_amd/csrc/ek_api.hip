@@ -175,43 +175,42 @@ ek_status ek_ctx::read_scalars(PoissonScalars* out) {
   return EK_OK;
 }
 
-// Red-black SOR with the Chebyshev schedule on A psi = b + shift (the shift
-// is already in ps).  The residual is tested after every `check_every`
-// iterations; iterations are enqueued in batches ahead of the test and turn
-// into no-ops once the device-side flag is set.
 int ek_ctx::residual_launch(const double* bb, const double* x) {
   const SiteGrid g = site_grid(p.nx, p.ny, p.nz, bx_sites);
   if (insulating()) return launch_residual_neu(x, bb, mask, ps, partials, dims, g, stream);
   return launch_residual(x, bb, ps, partials, dims, g, stream);
 }
 
+// Iterations times 1 + 1 / check_every up to which a solve is cheaper by single
+// launches (64^3: 8 iterations tested one by one 180 us by single launches, 223
+// by batches; 12: 239 and 241; 16 tested by fours 195 and 235, 24 263 and 251).
+constexpr double SOR_BRIEF = 20.0;
+
+// Red-black SOR with the Chebyshev schedule on A psi = b + shift (the shift
+// is already in ps), in batches of one launch where the lattice has a plan
+// (kernels_sor.hip), else in launches of half sweeps: iterations are enqueued
+// in batches ahead of the test, which follows every `check_every` of them, and
+// turn into no-ops once the device-side flag is set.
 ek_status ek_ctx::sor_solve(const double* bb, double* x, PoissonScalars h, int& iters, double& res,
                            double& res0) {
   const SiteGrid cg = colour_grid(p.nx, p.ny, p.nz, bx_colour);
   const bool neu = insulating();
   const double rj = jacobi_radius();
   ek_status st = EK_OK;
-  int it = 0;
+  int it = 0, sweeps = 0;
   double omega = 1.0;
-  bool first = true;
   const int ce = p.poisson_check_every;
-  if (!h.done && sor_team_solve(bb, x, h, it, st)) {
-    if (st) return st;
-  }
-  // the same half sweeps in launches of their own (larger lattices)
-  for (int k = 0; k < 2 * it; ++k) {
-    omega = first ? 1.0 / (1.0 - 0.5 * rj * rj) : 1.0 / (1.0 - 0.25 * rj * rj * omega);
-    first = false;
-  }
-  int batch = std::max(ce, ((last_iters - it + ce - 1) / ce) * ce);
-  while (!h.done && it < p.poisson_max_iter) {
-    const int nrun = std::min(batch, p.poisson_max_iter - it);
-    for (int k = 0; k < nrun; ++k) {
+  auto next_omega = [&] {
+    omega = sweeps == 0 ? 1.0 / (1.0 - 0.5 * rj * rj) : 1.0 / (1.0 - 0.25 * rj * rj * omega);
+    ++sweeps;
+  };
+  auto launch_iterations = [&](int n) -> ek_status {
+    n = std::min(n, p.poisson_max_iter - it);
+    for (int k = 0; k < n; ++k) {
       for (int colour = 0; colour < 2; ++colour) {
         if (neu) launch_sor_half_neu(x, bb, mask, ps, colour, omega, dims, cg, stream);
         else launch_sor_half(x, bb, ps, colour, omega, dims, cg, stream);
-        omega = first ? 1.0 / (1.0 - 0.5 * rj * rj) : 1.0 / (1.0 - 0.25 * rj * rj * omega);
-        first = false;
+        next_omega();
       }
       ++it;
       if (it % ce == 0 || it == p.poisson_max_iter) {
@@ -219,7 +218,22 @@ ek_status ek_ctx::sor_solve(const double* bb, double* x, PoissonScalars h, int& 
         launch_residual_final(partials, nr, p.poisson_tol, it, 0, ps, stream);
       }
     }
-    st = read_scalars(&h);
+    return read_scalars(&h);
+  };
+  int batch = std::max(ce, ((last_iters + ce - 1) / ce) * ce);
+  // as short as the last solve was: as many single launches first
+  if (!h.done && sor.ok && last_iters > 0 && last_iters * (1.0 + 1.0 / ce) <= SOR_BRIEF) {
+    st = launch_iterations(batch);
+    if (st) return st;
+    batch = ce;
+  }
+  if (!h.done && it < p.poisson_max_iter && sor_team_solve(bb, x, h, it, omega, st)) {
+    if (st) return st;
+    while (sweeps < 2 * it) next_omega();
+    batch = std::max(ce, ((last_iters - it + ce - 1) / ce) * ce);
+  }
+  while (!h.done && it < p.poisson_max_iter) {
+    st = launch_iterations(batch);
     if (st) return st;
     batch = ce;
   }

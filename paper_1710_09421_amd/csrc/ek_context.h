@@ -178,7 +178,8 @@ struct ek_ctx {
                       double& res0);
   ek::SorPlan sor;
   void sor_setup(char* mem);
-  bool sor_team_solve(const double* b, double* x, ek::PoissonScalars& h, int& it, ek_status& st);
+  bool sor_team_solve(const double* b, double* x, ek::PoissonScalars& h, int& it, double omega,
+                      ek_status& st);
   // With start_norms the start's residual has not been evaluated: the first
   // cycle does it (mg_start_in_cycle), before anything else of the cycle.
   ek_status mg_solve(const double* b, double* x, ek::PoissonScalars h, int& iters, double& res,

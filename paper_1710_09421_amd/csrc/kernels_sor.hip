@@ -56,6 +56,7 @@ constexpr int SOR_WAVES = SOR_THREADS / 64;
 constexpr int SOR_MAX_BATCH = 256;
 constexpr int SOR_NEAR = 12;          // iterations left within which a batch crosses the end
 constexpr int SOR_SHORT = 4;          // else it stops this many before the expected end
+constexpr int SOR_AFTER = 24;         // iterations expected after single launches
 constexpr int SOR_MAX_ITEMS = 4;      // sites of a colour per thread
 constexpr int SOR_MAX_TAKE = 8;       // values a thread takes per iteration
 constexpr int SOR_MAX_GROUPS = 256;   // one workgroup per compute unit
@@ -90,6 +91,8 @@ struct SorArgs {
   int spin_limit;     // looks in vain after which a wait gives up
   double* part;       // [2][iteration of the batch][workgroup]: likewise
   int launch;
+  int start;          // iterations that the caller has run
+  double omega;       // relaxation factor of the half sweep after them
   int first;          // length of the first batch
   int nx, ny, nz, ty, tz, gy, gz;
   int max_iter, every;
@@ -125,9 +128,10 @@ __device__ inline SorControl sor_verdict(const SorArgs& a, double* rel) {
   if (c.aborted) c.state = SOR_LIMIT;
   if (c.state == SOR_START) {
     c.state = SOR_RAN;
-    c.cur = c.base = 0;
+    c.cur = 0;
+    c.base = a.start;
     c.n = a.first;
-    c.omega = 1.0;
+    c.omega = a.omega;
     return c;
   }
   if (c.state == SOR_REPLAYED) {
@@ -606,9 +610,11 @@ extern "C" void ek_test_sor_batches(ek_ctx* ctx, int spin_limit, int limit_from,
 }
 
 // The solve of sor_solve by batches in one launch each; false (and x as it
-// was) where that is not possible here.  `it` iterations are in x afterwards;
-// the caller goes on from there where h says that the solve is not done.
-bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int& it, ek_status& st) {
+// was) where that is not possible here.  `it` iterations are in x, with `omega`
+// for the half sweep after them, and `it` of them afterwards; the caller goes on
+// from there where h says that the solve is not done.
+bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int& it, double omega,
+                            ek_status& st) {
   st = EK_OK;
   if (!sor.ok) return false;
   SorArgs a{};
@@ -627,6 +633,8 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
   a.tz = sor.tz;
   a.gy = sor.gy;
   a.gz = sor.gz;
+  a.start = it;
+  a.omega = omega;
   a.max_iter = p.poisson_max_iter;
   a.every = p.poisson_check_every;
   a.rj = jacobi_radius();
@@ -672,9 +680,9 @@ bool ek_ctx::sor_team_solve(const double* bb, double* x, PoissonScalars& h, int&
   SorControl c{};
   // full batches, the two that end the solve, its second run and the verdict
   // on that (a launch with nothing left to run ends at once)
-  const int expect = last_iters > 0 ? last_iters : 200;
+  const int expect = it > 0 ? SOR_AFTER : last_iters > 0 ? last_iters : 200;
   a.first = std::min({expect > SOR_NEAR ? expect - SOR_SHORT : expect + 2, SOR_MAX_BATCH,
-                      p.poisson_max_iter});
+                      p.poisson_max_iter - it});
   int ahead = expect / SOR_MAX_BATCH + 4;
   bool refused = false;
   while (c.state < SOR_FINAL && !c.aborted && !refused) {
