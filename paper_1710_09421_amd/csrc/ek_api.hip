@@ -296,6 +296,14 @@ ek_status ek_ctx::learned_start(const double* bb, double* x, PoissonScalars* h) 
   return initial_residual(bb, x, h);
 }
 
+// Takes the rounding of its mean out of the right-hand side b where the sums h
+// of a residual ask for it (rhs_mean_rounded).
+bool ek_ctx::neutralize(const PoissonScalars& h) {
+  if (h.done || insulating() || !rhs_mean_rounded(h, p.poisson_tol, dims.n)) return false;
+  launch_neutral(b, ps, partials, dims, site_grid(p.nx, p.ny, p.nz, bx_sites), stream);
+  return true;
+}
+
 // The time loop solves directly where the sides have a plan; a stand-alone
 // solve keeps the multigrid cycles, whose number its callers compare starts
 // by, unless the box has no coarser level (hundreds of SOR sweeps a cycle:
@@ -327,6 +335,8 @@ ek_status ek_ctx::poisson(const double* bb, double* x, bool learned, int& iters,
   if (st) return st;
   if (direct) return spectral_solve(bb, x, h, iters, res, res0, false);
   if (p.poisson_method == EK_POISSON_MG) return mg_solve(bb, x, h, iters, res, res0);
+  if (neutralize(h)) st = initial_residual(bb, x, &h);
+  if (st) return st;
   return sor_solve(bb, x, h, iters, res, res0);
 }
 

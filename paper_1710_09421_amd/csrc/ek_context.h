@@ -213,6 +213,7 @@ struct ek_ctx {
   void spectral_cycle(const double* b, double* x, bool start);
   bool defer_set = false;           // the last step's boxes are still flagged MASK_DEFER
   bool direct_solve() const;        // a solve takes it
+  bool neutralize(const ek::PoissonScalars& h);   // of the right-hand side `b`
   ek_status spectral_begin(const double* b, double* x);
   ek_status spectral_look(ek::PoissonScalars& h);
   ek_status spectral_solve(const double* b, double* x, ek::PoissonScalars h, int& iters,
@@ -244,10 +245,9 @@ struct ek_ctx {
   // Box gather and chain kernel on the context stream (stamping `chain_end`
   // when given).  With `overlap` the box nodes are flagged MASK_DEFER and
   // side_fork is recorded after the gather, for the lattice update that the
-  // caller runs beside the chain on side_stream.
+  // caller runs beside the chain on side_stream.  With `guard` (launched ahead
+  // of the solve's result) the chain skips itself unless guard->done.
   template <typename T>
-  // guard: launched ahead of the solve's result, the chain skips itself
-  // unless guard->done
   ek_status beads_advance(bool overlap, hipEvent_t chain_end, const ek::PoissonScalars* guard);
   ek_status beads_check();
 };

@@ -219,6 +219,15 @@ void launch_psi_shift_neu(double* psi, const uint32_t* mask, const PoissonScalar
 void launch_fill(double* x, double v, long long n, hipStream_t s);
 void launch_ps_reset(PoissonScalars* ps, double shift, hipStream_t s);
 void launch_ps_rearm(PoissonScalars* ps, hipStream_t s);
+// Right-hand sides whose variation is lost beside their mean: b + shift then has
+// a mean of its own, the shift's rounding at every site, which is no potential's
+// charge and which no iteration can take out of the residual (SOR spreads it over
+// the colours besides).  True where, by the sums of a residual, it may keep the
+// residual above the tolerance; launch_neutral then removes it: b + shift - mean
+// into b, and the shift is 0.
+bool rhs_mean_rounded(const PoissonScalars& h, double tol, long long n);
+void launch_neutral(double* b, PoissonScalars* ps, double* partials, Dims d, const SiteGrid& g,
+                    hipStream_t s);
 void launch_rhs_copy(const double* b, const PoissonScalars* ps, double* out, long long n,
                      hipStream_t s);
 void launch_rho_to_b(const double* rho, double* b, double* partials, double inv_eps, Dims d,

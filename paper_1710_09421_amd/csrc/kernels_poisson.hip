@@ -9,6 +9,9 @@
 // Every kernel first reads the converged flag and returns at once when it is
 // set: the host enqueues iterations ahead of the convergence test and the
 // iterations past convergence do no work.
+#include <algorithm>
+#include <cmath>
+
 #include "ek_internal.h"
 #include "reduce.h"
 
@@ -471,7 +474,50 @@ __global__ __launch_bounds__(BLOCK) void k_rhs_copy(const double* __restrict__ b
   const long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (r < n) out[r] = b[r] + ps->shift;
 }
+
+// b + shift into b (APPLY = false, with its partial sums), then less its mean.
+template <bool APPLY>
+__global__ __launch_bounds__(BLOCK) void k_neutral(double* __restrict__ b,
+                                                   const PoissonScalars* __restrict__ ps,
+                                                   double* __restrict__ partials, double inv_n,
+                                                   Dims d) {
+  const int x = blockIdx.x * blockDim.x + threadIdx.x;
+  const int y = blockIdx.y * blockDim.y + threadIdx.y;
+  const int z = blockIdx.z;
+  double acc[1] = {0.0};
+  if (x < d.nx && y < d.ny) {
+    const long long r = ((long long)z * d.ny + y) * d.nx + x;
+    const double v = APPLY ? b[r] - ps->psum * inv_n : b[r] + ps->shift;
+    b[r] = v;
+    acc[0] = v;
+  }
+  if constexpr (!APPLY)
+    block_partials<1>(acc, partials, blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z),
+                      gridDim.x * gridDim.y * gridDim.z);
+}
+__global__ __launch_bounds__(1024) void k_neutral_sum(const double* __restrict__ partials,
+                                                      int nblocks, PoissonScalars* ps) {
+  double t[1];
+  block_sums_1024<1>(partials, nblocks, t);
+  if (threadIdx.x == 0) {
+    ps->psum = t[0];      // until the next residual
+    ps->shift = 0.0;
+  }
+}
 }  // namespace
+
+bool rhs_mean_rounded(const PoissonScalars& h, double tol, long long n) {
+  constexpr double unit = 2.2e-16;   // a rounding of the shift, at every site
+  return unit * std::fabs(h.shift) * std::sqrt(double(n)) >
+         0.05 * std::max(tol, 1e-13) * std::sqrt(h.b2);
+}
+void launch_neutral(double* b, PoissonScalars* ps, double* partials, Dims d, const SiteGrid& g,
+                    hipStream_t s) {
+  const double inv_n = 1.0 / double(d.n);
+  hipLaunchKernelGGL(k_neutral<false>, g.grid, g.block, 0, s, b, ps, partials, inv_n, d);
+  hipLaunchKernelGGL(k_neutral_sum, dim3(1), dim3(1024), 0, s, partials, g.nblocks(), ps);
+  hipLaunchKernelGGL(k_neutral<true>, g.grid, g.block, 0, s, b, ps, partials, inv_n, d);
+}
 void launch_ps_rearm(PoissonScalars* ps, hipStream_t s) {
   hipLaunchKernelGGL(k_ps_rearm, dim3(1), dim3(64), 0, s, ps);
 }

@@ -623,6 +623,7 @@ ek_status ek_ctx::spectral_solve(const double* bb, double* x, PoissonScalars h, 
     if (st) return st;
     it = 1;
   }
+  if (it < p.poisson_max_iter) neutralize(h);
   while (!h.done && it < p.poisson_max_iter) {
     ++it;
     spectral_cycle(bb, x, false);

@@ -117,6 +117,13 @@ extern "C" ek_status ek_poisson_solve_noalloc(const ek_params* p, const double* 
   PoissonScalars h{};
   ek_status st = read_scalars(ps, s, &h);
   if (st) return st;
+  if (!h.done && rhs_mean_rounded(h, p->poisson_tol, d.n)) {
+    launch_neutral(b, ps, partials, d, g, s);
+    nr = launch_residual(dev_psi, b, ps, partials, d, g, s);
+    launch_residual_final(partials, nr, p->poisson_tol, 0, 1, ps, s);
+    st = read_scalars(ps, s, &h);
+    if (st) return st;
+  }
   // iterations in batches of check_every, each ended by a residual test;
   // iterations after convergence are skipped on the device
   const double rj = p->rho_jacobi > 0.0
