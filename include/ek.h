@@ -492,10 +492,10 @@ ek_status ek_unet_read_loss(ek_unet* net, double* mean_loss, int64_t* count);
  * launch of a step (charge pass, direct Poisson solve as EK_POISSON_MG's time
  * loop, chain, fused lattice step) covers all replicas; the host enqueues the
  * steps of a call and then looks at the replicas, each of which has its own
- * convergence test.  Boxes without a direct solver (an odd side or one beyond
- * 960) and a poisson_max_iter below 20 take one persistent launch per
- * call instead, in which a team of 1, 2 or 4 workgroups per replica runs the
- * whole time loop of Fig. 1 with multigrid cycles.  The solves start from the
+ * convergence test.  Boxes without a direct solver (a side beyond 960) and a
+ * poisson_max_iter below 20 take one persistent launch per call instead, in
+ * which a team of 1, 2 or 4 workgroups per replica runs the whole time loop of
+ * Fig. 1 with multigrid cycles.  The solves start from the
  * previous solution, or from the extrapolated one when the base warm_start is
  * EK_WS_EXTRAP (other values: the previous solution); all other parameters
  * come from the base ek_params except the applied field.
@@ -530,10 +530,10 @@ ek_status ek_ensemble_set_replica(ek_ensemble* ens, int32_t r, const double* E_e
                                   const double* vel, const double* charge,
                                   const ek_polymer_params* pp);
 
-/* n_steps steps of every replica; returns after the stream is synchronised.  EK_ENOCONV if a replica's Poisson solve did not
- * reach the tolerance in poisson_max_iter cycles, EK_EUNSTABLE if a replica's
- * mass became non-finite or its chain failed (ek_ensemble_last_error names
- * the replica). */
+/* n_steps steps of every replica; returns after the stream is synchronised.
+ * EK_ENOCONV if a replica's Poisson solve did not reach the tolerance in
+ * poisson_max_iter cycles, EK_EUNSTABLE if a replica's mass became non-finite
+ * or its chain failed (ek_ensemble_last_error names the replica). */
 ek_status ek_ensemble_step(ek_ensemble* ens, int32_t n_steps);
 
 ek_status ek_ensemble_get_moments(ek_ensemble* ens, int32_t r, int32_t species, double* n,

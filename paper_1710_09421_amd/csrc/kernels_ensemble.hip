@@ -1,9 +1,9 @@
 // Ensemble of uneven replicas: the host side, and the persistent kernel that
 // takes the ensembles which the launched steps (kernels_replicas.hip) do not.
 //
-// In the persistent launch one workgroup owns one replica for the whole call: it runs every phase of
-// the time step (Fig. 1) on its replica with __syncthreads as the only
-// barrier — bead charge deposit, charge pass, multigrid Poisson solve with the
+// In the persistent launch one workgroup owns one replica for the whole call:
+// it runs every phase of the time step (Fig. 1) on its replica with
+// __syncthreads as the only barrier — bead charge deposit, charge pass, multigrid Poisson solve with the
 // replica's own convergence test, bead boxes and chain substeps, fused
 // collide-and-stream — and loops over the steps.  No workgroup ever waits for
 // another, so replicas with more Poisson cycles or longer chains do not hold

@@ -411,7 +411,7 @@ def from_workload(wl, precision=EK_FP32, poisson_method=EK_POISSON_SOR, poisson_
 
 
 class Ensemble:
-    """Replicas of one geometry advanced by one persistent launch per step call."""
+    """Replicas of one geometry advanced together."""
 
     def __init__(self, params, n_rep, max_beads=0, stream=None):
         import torch
